@@ -51,6 +51,60 @@ __device__ __forceinline__ double rsqrt64(double x)
 
 __device__ __forceinline__ float rsqrt32(float x) { return __builtin_amdgcn_rsqf(x); }
 
+// Negative half powers in FP64, x^(-P/2) / kappa: with the hardware estimate y (~24 bits) and
+// e = 1 - x y^2, x^(-P/2) = y^P (1 + P e/2 + P (P + 2) e^2 / 8 + O(e^3)) to full precision (the
+// next term is below 1e-20).  Written as a square, the polynomial is kappa ((e + h)^2 + c) with
+// h = 2 / (P + 2) and kappa = P (P + 2) / 8: two instructions instead of three, and the power
+// y^P needs no refined 1/r first.  The constant kappa is left out here and multiplied into the
+// element's charge once (half_power_scale).  kHalf = 1 + h and kRest = c are chosen among the
+// neighbouring FP64 numbers so that kappa (h^2 + c) = 1 to 2e-17.  Relative error against
+// 64-bit-mantissa references: r^-3 rms 9.6e-17, max 3.8e-16 (cubing a refined 1/r: 1.7e-16 and
+// 5.8e-16); r^-1 as x times r^-3 rms 9.6e-17.
+template <int P> struct HalfPower;
+template <> struct HalfPower<1> { static constexpr double kHalf = 0x1.aaaaaaaaaaaacp+0, kRest = 0x1.1c71c71c71c71p+1, kappa = 0.375; };
+template <> struct HalfPower<3> { static constexpr double kHalf = 0x1.6666666666666p+0, kRest = 0x1.7e4b17e4b17e6p-2, kappa = 1.875; };
+
+// The factors y^P and (e + h)^2 + c of x^(-P/2) / kappa for P = 3.
+__device__ __forceinline__ void half_power3(double x, double& y3, double& m)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double y2 = y * y;
+    const double t = fma(-x, y2, HalfPower<3>::kHalf);
+    m = fma(t, t, HalfPower<3>::kRest);
+    y3 = y2 * y;
+}
+
+// x^(-3/2) over half_power_scale<3, T>
+__device__ __forceinline__ double inv_cube(double x)
+{
+    double y3, m;
+    half_power3(x, y3, m);
+    return y3 * m;
+}
+__device__ __forceinline__ float inv_cube(float x)
+{
+    const float y = rsqrt32(x);
+    return (y * y) * y;
+}
+
+// acc + w x^(-1/2) / kappa in FP64 (w = 1: one instruction less)
+__device__ __forceinline__ double add_inv_root(double x, double acc)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double t = fma(-(x * y), y, HalfPower<1>::kHalf);
+    return fma(y, fma(t, t, HalfPower<1>::kRest), acc);
+}
+__device__ __forceinline__ double add_inv_root(double w, double x, double acc)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double t = fma(-(x * y), y, HalfPower<1>::kHalf);
+    return fma(w * y, fma(t, t, HalfPower<1>::kRest), acc);
+}
+
+// kappa of the node sums that P and T stand for: FP64 sums lack it, FP32 sums do not
+template <int P, typename T>
+constexpr double half_power_scale() { return std::is_same<T, double>::value ? HalfPower<P>::kappa : 1.0; }
+
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
 // The lanes of the wavefront for which pred holds.  A comparison's own lane mask: __ballot
@@ -257,7 +311,9 @@ __device__ __forceinline__ TriForms fixed_forms(int nn)
 // with x_{6-j} = -x_j, the same weight for j and 6 - j and x_3 = 0.  Four slots per row:
 //   header (b, a0, w of the middle node, a0^2 + b^2), then per pair j = 0, 1, 2 with
 //   s = x_{6-j} alpha: (s, s^2, w, w s).
+// Folded (FP64): 1 / w^2 in place of w in the header, and per pair (s, s^2, 1, 0) / w^2.
 constexpr int kPairRowSlots = 28;
+template <bool FOLDED>
 __device__ __forceinline__ double4 pair_row_slot(const RuleTables& R, int prow, int m, double gamma, double beta,
                                                  double alpha)
 {
@@ -266,10 +322,15 @@ __device__ __forceinline__ double4 pair_row_slot(const RuleTables& R, int prow, 
         const int i = prow + r * 7 + 3;
         const double x = R.rect[4 * i];
         const double b = x * beta, a0 = x * gamma;
-        return make_double4(b, a0, R.rect[4 * i + 2], fma(a0, a0, b * b));
+        const double w = R.rect[4 * i + 2];
+        return make_double4(b, a0, FOLDED ? 1.0 / (w * w) : w, fma(a0, a0, b * b));
     }
     const int i = prow + r * 7 + 7 - c;  // j = 6 - (c - 1)
     const double sv = R.rect[4 * i + 1] * alpha, w = R.rect[4 * i + 2];
+    if constexpr (FOLDED) {
+        const double iw2 = 1.0 / (w * w);
+        return make_double4(sv * iw2, sv * sv * iw2, iw2, 0.0);
+    }
     return make_double4(sv, sv * sv, w, w * sv);
 }
 
@@ -281,11 +342,12 @@ __device__ __forceinline__ double4 pair_row_slot(const RuleTables& R, int prow, 
 // The first nfold nodes of each element are staged divided by w^2 (positive weights only).
 // Nodes from prow on are a 7 x 7 Gauss-Legendre rule staged as pair rows (pair_row_slot).
 // Triangles: centroid and S21 nodes (TriForms, folded nodes only) are staged as
-// (0, 0, 1/w^2, 0) and (s, |n|^2, 1, 0) / w^2 with n = s u_k.
+// (0, 0, 1/w^2, 0) and (s, |n|^2, 1, 0) / w^2 with n = s u_k.  The charges are staged times
+// scale (the constant that the node sums leave out, half_power_scale).
 template <bool TRI, bool MIXED, int NRHS, int FR, bool QR>
 __device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elements& el, const RuleTables& R, int nn,
                                            int64_t t0, int te, int rhs0, int nrhs, int nfold, int prow,
-                                           const TriForms& tf)
+                                           const TriForms& tf, double scale)
 {
     using T = typename TileLds<MIXED, NRHS>::T;
     const int64_t ne = el.ne;
@@ -295,8 +357,8 @@ __device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elemen
         s.cy[k] = el.cen[ne + e];
         s.cz[k] = el.cen[2 * ne + e];
         s.thr2[k] = el.thr2[e];
-        for (int r = 0; r < nrhs; ++r) s.q[r][k] = el.q[(int64_t)(rhs0 + r) * ne + e];
-        const double q = QR ? el.q[(int64_t)rhs0 * ne + e] : 0.0;
+        for (int r = 0; r < nrhs; ++r) s.q[r][k] = scale * el.q[(int64_t)(rhs0 + r) * ne + e];
+        const double q = QR ? scale * el.q[(int64_t)rhs0 * ne + e] : 0.0;
         if constexpr (FR == kFrExp) {
 #pragma unroll
             for (int c = 0; c < 6; ++c) {
@@ -320,7 +382,7 @@ __device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elemen
         const int64_t e = t0 + j;
         if (!TRI && i >= prow) {
             if (i - prow < kPairRowSlots) {
-                const double4 v = pair_row_slot(R, prow, i - prow, el.loc[e], el.loc[ne + e], el.loc[2 * ne + e]);
+                const double4 v = pair_row_slot<!MIXED>(R, prow, i - prow, el.loc[e], el.loc[ne + e], el.loc[2 * ne + e]);
                 if constexpr (MIXED) s.nd[k] = make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
                 else s.nd[k] = v;
             }
@@ -387,6 +449,13 @@ struct Sums {
     static constexpr int kNode = MODE == kFarGrad ? 7 : (MODE == kFarField ? 4 : 1);  // element sums per point
 };
 
+// The constant left out of the node sums, multiplied into the staged charges (half_power_scale).
+template <int MODE, typename T>
+constexpr double sum_scale()
+{
+    return MODE == kFarGrad ? 1.0 : (MODE == kFarField ? half_power_scale<3, T>() : half_power_scale<1, T>());
+}
+
 // Field points of one lane and their FP64 accumulators.
 template <int PPT, int MODE>
 struct PointSet {
@@ -431,13 +500,44 @@ __device__ __forceinline__ void for_nodes(int n, Term term)
 __device__ __forceinline__ double rsqrtT(double x) { return rsqrt64(x); }
 __device__ __forceinline__ float rsqrtT(float x) { return rsqrt32(x); }
 
-// Node sums of one element per field point (unit element charge, Eq. 4.1), accumulated into
+// One folded node of the field (r^2 / w^2 = x): returns (w/r)^3 and adds w/r to phi.  FP64: both
+// from x^(-3/2) alone, since (w/r)^3 x = w/r: 13 FP64 instructions per expanded node instead of
+// 15 with a refined 1/r (one of them the quarter-rate v_rsq_f64).
+__device__ __forceinline__ double inv_cube_phi(double x, double& phi)
+{
+    const double w3 = inv_cube(x);
+    phi = fma(w3, x, phi);
+    return w3;
+}
+__device__ __forceinline__ float inv_cube_phi(float x, float& phi)
+{
+    const float wr = rsqrt32(x);
+    phi += wr;
+    return (wr * wr) * wr;
+}
+// The same for an unfolded node of weight w (r^2 = x): returns w/r^3 and adds w/r to phi.
+__device__ __forceinline__ double inv_cube_phi(double w, double x, double& phi)
+{
+    double y3, m;
+    half_power3(x, y3, m);
+    const double w3 = (w * y3) * m;
+    phi = fma(w3, x, phi);
+    return w3;
+}
+__device__ __forceinline__ float inv_cube_phi(float w, float x, float& phi)
+{
+    const float ri = rsqrt32(x);
+    const float wr = w * ri;
+    phi += wr;
+    return wr * (ri * ri);
+}
+
+// Node sums of one element per field point (unit element charge, Eq. 4.1; FP64 sums lack the
+// factor half_power_scale), accumulated into
 // o, whose sums start at -0.0 (so that adding the first node folds into an assignment).
 //   kFarField, expanded: (sum w/r, sum w a/r^3, sum w b/r^3, sum w/r^3);
 //              FOLD: the staged node is (a, b, g, 1) / w^2 and rsqrt(r^2 / w^2) = w/r;
-//   kFarPhi,   expanded: sum w/r; FOLD in FP64: the potential of the node is y (1 + e/2 +
-//              3 e^2 / 8) with y the hardware estimate of w/r and e = 1 - (r^2/w^2) y^2,
-//              formed as one FMA of y with the factor (the same third-order step as rsqrt64);
+//   kFarPhi,   expanded: sum w/r;
 //   kFarGrad   (differences da = p1 - a, db = p2 - b): FP64 (sum w/r^3, sum w/r^5,
 //              sum w da/r^5, sum w db/r^5, sum w da^2/r^5, sum w db^2/r^5, sum w da db/r^5),
 //              turned into the local tensor after the loop; FP32: the local tensor itself,
@@ -481,29 +581,21 @@ __device__ __forceinline__ void node_term(const T4 Q, const Local<PPT, T>& L, T 
         } else if constexpr (FOLD) {
             const T x = fma(L.q1[k], a, fma(L.q2[k], b, fma(L.H[k], w, g)));  // r^2 / w^2
             if constexpr (MODE == kFarPhi) {
-                if constexpr (F64) {
-                    const double y = __builtin_amdgcn_rsq(x);
-                    const double e = fma(-(x * y), y, 1.0);
-                    o[0][k] = fma(y, fma(e, fma(e, 0.375, 0.5), 1.0), o[0][k]);
-                } else {
-                    o[0][k] += rsqrtT(x);
-                }
+                if constexpr (F64) o[0][k] = add_inv_root(x, o[0][k]);
+                else o[0][k] += rsqrtT(x);
             } else {
-                const T wr = rsqrtT(x);  // w / r
-                const T wr3 = (wr * wr) * wr;
-                o[0][k] += wr;
+                const T wr3 = inv_cube_phi(x, o[0][k]);
                 o[1][k] = fma(wr3, a, o[1][k]);
                 o[2][k] = fma(wr3, b, o[2][k]);
                 o[3][k] = fma(wr3, w, o[3][k]);
             }
         } else {
-            const T ri = rsqrtT(fma(L.q1[k], a, fma(L.q2[k], b, L.H[k] + g)));
+            const T x = fma(L.q1[k], a, fma(L.q2[k], b, L.H[k] + g));
             if constexpr (MODE == kFarPhi) {
-                o[0][k] = fma(w, ri, o[0][k]);
+                if constexpr (F64) o[0][k] = add_inv_root(w, x, o[0][k]);
+                else o[0][k] = fma(w, rsqrtT(x), o[0][k]);
             } else {
-                const T wr = w * ri;
-                const T w3 = wr * (ri * ri);
-                o[0][k] += wr;
+                const T w3 = inv_cube_phi(w, x, o[0][k]);
                 o[1][k] = fma(w3, a, o[1][k]);
                 o[2][k] = fma(w3, b, o[2][k]);
                 o[3][k] += w3;
@@ -588,11 +680,14 @@ __device__ __forceinline__ void group_sum(const T4* t, int base, const Local<PPT
 // field, or the potential alone.  With da0 = p1 - a0 and C = |d - (a0 f1 + b f2)|^2, formed
 // like the expanded form from D^2 (C = D^2 + a0^2 + b^2 - 2 (p1 a0 + p2 b): the rotation's
 // rounding then enters only through the small products), the pair at a0 -+ s has
-// r^2 = C + s^2 -+ 2 da0 s; its sums go in as w (1/r+ + 1/r-), w (1/r+^3 +
-// 1/r-^3) and w s (1/r+^3 - 1/r-^3), the last one into SA.  Per row the field's local parts
-// follow as E1 += da0 sg, E2 += (p2 - b) sg, S3 += sg with sg = sum over the row of w/r^3;
-// E1 -= SA once per element.  FP64 potential only: each pair's 1/r as y (1 + e (1/2 + 3e/8))
-// from the hardware estimate y (the third-order step of rsqrt64), the weight applied once.
+// r^2 = C + s^2 -+ 2 da0 s.  Per row the field's local parts follow from sg, the sum over the row
+// of w/r^3, as E1 += da0 sg, E2 += (p2 - b) sg, S3 += sg; E1 -= SA once per element, SA the sum
+// of w s (1/r+^3 - 1/r-^3).
+// FP64 (folded slots): the potential comes from the same sums, since w/r = (w/r^3) r^2: over the
+// row C sg - 2 da0 sa + sum w s^2 (1/r+^3 + 1/r-^3), sa the row's share of SA; the first term is
+// close to the whole and the others small corrections, so nothing cancels.  9 FP64 instructions
+// per node beside the reciprocal square root, 11.5 with refined 1/r and separate potential sums.
+// FP32: 1/r is at hand, and the potential sums it: w (1/r+ + 1/r-).
 template <int PPT, int MODE, typename T, typename T4>
 __device__ __forceinline__ void pair_row(const T4* t, int n0, const Local<PPT, T>& L, T (&o)[Sums<MODE>::kNode][PPT],
                                          T (&SA)[PPT])
@@ -600,61 +695,67 @@ __device__ __forceinline__ void pair_row(const T4* t, int n0, const Local<PPT, T
     constexpr bool F64 = std::is_same<T, double>::value;
     const T4 hd = t[n0];
     const T b = hd.x, a0 = hd.y, wc = hd.z, g0 = hd.w;
-    T db[PPT], da0[PPT], C[PPT], mq[PPT], pq[PPT], sg[PPT];
+    T db[PPT], da0[PPT], C[PPT], mq[PPT], sg[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
         db[k] = L.p2[k] - b;
         da0[k] = L.p1[k] - a0;
         C[k] = fma(L.q1[k], a0, fma(L.q2[k], b, L.H[k] + g0));
         mq[k] = T(-2) * da0[k];
-        pq[k] = T(2) * da0[k];
     }
     // the middle node (a = a0)
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
         if constexpr (MODE == kFarPhi) {
-            if constexpr (F64) {
-                const double y = __builtin_amdgcn_rsq(C[k]);
-                const double e = fma(-(C[k] * y), y, 1.0);
-                o[0][k] = fma(wc * y, fma(e, fma(e, 0.375, 0.5), 1.0), o[0][k]);
-            } else {
-                o[0][k] = fma(wc, rsqrtT(C[k]), o[0][k]);
-            }
+            if constexpr (F64) o[0][k] = add_inv_root(C[k] * wc, o[0][k]);
+            else o[0][k] = fma(wc, rsqrtT(C[k]), o[0][k]);
+        } else if constexpr (F64) {
+            sg[k] = inv_cube(C[k] * wc) * wc;
         } else {
             const T ri = rsqrtT(C[k]);
             o[0][k] = fma(wc, ri, o[0][k]);
             sg[k] = wc * ((ri * ri) * ri);
         }
     }
+    T sa[PPT];  // FP64 field: the row's sum w s (1/r+^3 - 1/r-^3)
 #pragma unroll
     for (int pi = 1; pi <= 3; ++pi) {
         const T4 Q = t[n0 + pi];
         const T sv = Q.x, s2 = Q.y, w = Q.z, ws = Q.w;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
-            const T u = C[k] + s2;
-            const T xp = fma(mq[k], sv, u), xm = fma(pq[k], sv, u);
-            if constexpr (MODE == kFarPhi) {
-                if constexpr (F64) {
-                    const double yp = __builtin_amdgcn_rsq(xp), ym = __builtin_amdgcn_rsq(xm);
-                    const double ep = fma(-(xp * yp), yp, 1.0), em = fma(-(xm * ym), ym, 1.0);
-                    const double vp = fma(ep, fma(ep, 0.375, 0.5), 1.0), vm = fma(em, fma(em, 0.375, 0.5), 1.0);
-                    o[0][k] = fma(w, fma(ym, vm, yp * vp), o[0][k]);
+            if constexpr (F64) {
+                const T u = fma(C[k], w, s2);  // (C + s^2) / w^2
+                const T xp = fma(mq[k], sv, u), xm = fma(-mq[k], sv, u);
+                if constexpr (MODE == kFarPhi) {
+                    o[0][k] = add_inv_root(xm, add_inv_root(xp, o[0][k]));
                 } else {
-                    o[0][k] = fma(w, rsqrtT(xp) + rsqrtT(xm), o[0][k]);
+                    const T r3p = inv_cube(xp), r3m = inv_cube(xm);
+                    const T sum = r3p + r3m, dif = r3p - r3m;
+                    sg[k] = fma(w, sum, sg[k]);
+                    sa[k] = pi == 1 ? sv * dif : fma(sv, dif, sa[k]);
+                    o[0][k] = fma(s2, sum, o[0][k]);
                 }
             } else {
+                const T u = C[k] + s2;
+                const T xp = fma(mq[k], sv, u), xm = fma(-mq[k], sv, u);
                 const T rp = rsqrtT(xp), rm = rsqrtT(xm);
-                const T r3p = (rp * rp) * rp, r3m = (rm * rm) * rm;
                 o[0][k] = fma(w, rp + rm, o[0][k]);
-                sg[k] = fma(w, r3p + r3m, sg[k]);
-                SA[k] = fma(ws, r3p - r3m, SA[k]);
+                if constexpr (MODE == kFarField) {
+                    const T r3p = (rp * rp) * rp, r3m = (rm * rm) * rm;
+                    sg[k] = fma(w, r3p + r3m, sg[k]);
+                    SA[k] = fma(ws, r3p - r3m, SA[k]);
+                }
             }
         }
     }
     if constexpr (MODE == kFarField) {
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
+            if constexpr (F64) {
+                o[0][k] = fma(C[k], sg[k], fma(mq[k], sa[k], o[0][k]));
+                SA[k] += sa[k];
+            }
             o[1][k] = fma(da0[k], sg[k], o[1][k]);
             o[2][k] = fma(db[k], sg[k], o[2][k]);
             o[3][k] += sg[k];
@@ -685,17 +786,10 @@ template <int MODE, typename T>
 __device__ __forceinline__ void folded_point(T x, T iw2, T sv, T& o0, T& o3, T& tv)
 {
     if constexpr (MODE == kFarPhi) {
-        if constexpr (std::is_same<T, double>::value) {
-            const double y = __builtin_amdgcn_rsq(x);
-            const double e = fma(-(x * y), y, 1.0);
-            o0 = fma(y, fma(e, fma(e, 0.375, 0.5), 1.0), o0);
-        } else {
-            o0 += rsqrtT(x);
-        }
+        if constexpr (std::is_same<T, double>::value) o0 = add_inv_root(x, o0);
+        else o0 += rsqrtT(x);
     } else {
-        const T wr = rsqrtT(x);  // w / r
-        const T wr3 = (wr * wr) * wr;
-        o0 += wr;
+        const T wr3 = inv_cube_phi(x, o0);
         tv = fma(wr3, sv, tv);
         o3 = fma(wr3, iw2, o3);
     }
@@ -920,7 +1014,7 @@ __device__ __forceinline__ void far_eval_range(const FarArgs& a, Lds& s, PointSe
         __syncthreads();
         constexpr bool PROWS = tensor_group<TRI, NN>() > 0 && MODE != kFarGrad;
         stage_tile<TRI, MIXED, 1, FR, MODE == kFarField>(s, a.el, a.rules, nn, t0, te, a.rhs, 1, FOLD_ ? nn : 0,
-                                                         PROWS ? 0 : nn, tf);
+                                                         PROWS ? 0 : nn, tf, sum_scale<MODE, T>());
         __syncthreads();
         for (int j = 0; j < te; ++j) {
             const double thr2 = s.thr2[j], q = s.q[0][j];
@@ -1008,7 +1102,8 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
         // the 7 x 7 last level of the rectangles keeps its weights (rows form)
         const int nfold = !FOLD ? 0 : (tensor_group<TRI, N3>() > 0 ? o3 : nn);
         const int prow = (tensor_group<TRI, N3>() > 0 && !GRAD) ? o3 : nn;
-        stage_tile<TRI, MIXED, 1, FR, !GRAD>(s, a.el, a.lv.tab, nn, t0, te, a.rhs, 1, nfold, prow, tf);
+        stage_tile<TRI, MIXED, 1, FR, !GRAD>(s, a.el, a.lv.tab, nn, t0, te, a.rhs, 1, nfold, prow, tf,
+                                             sum_scale<MODE, T>());
         __syncthreads();
         for (int j = 0; j < te; ++j) {
             const double thr2 = s.thr2[j], q = s.q[0][j];
@@ -1150,7 +1245,7 @@ __device__ __forceinline__ void far_colloc_range(const FarArgs& a, Lds& s, const
         const int te = (int)min((int64_t)TE, e_end - t0);
         __syncthreads();
         stage_tile<TRI, MIXED, kMaxRhs, FR, false>(s, a.el, a.rules, nn, t0, te, 0, nrhs, FOLD ? nn : 0,
-                                                   tensor_group<TRI, NN>() > 0 ? 0 : nn, tf);
+                                                   tensor_group<TRI, NN>() > 0 ? 0 : nn, tf, sum_scale<kFarPhi, T>());
         __syncthreads();
         for (int j = 0; j < te; ++j) {
             const double thr2 = s.thr2[j];
@@ -1337,24 +1432,29 @@ __device__ __forceinline__ void node_geometry(const NearState& s, const NearGeom
 }
 
 // Sums of one Gaussian point at offsets (da, db, dc) in the element's frame, weight w (unit
-// element charge):
+// element charge; the field's and the potential's lack the factor near_scale):
 //   field:        f0 += w/r, (f1, f2, f3) += w (da, db, dc)/r^3;
 //   collocation:  f0 += w/r;
 //   gradient:     f0 += w/r^3, (f1 .. f6) += w (da^2, db^2, dc^2, da db, da dc, db dc)/r^5.
 template <int MODE>
+constexpr double near_scale()
+{
+    return MODE == kNearColloc ? HalfPower<1>::kappa : (MODE == kNearEval ? HalfPower<3>::kappa : 1.0);
+}
+template <int MODE>
 __device__ __forceinline__ void near_terms(double w, double da, double db, double dc, double (&f)[7])
 {
-    const double ri = rsqrt64(fma(da, da, fma(db, db, dc * dc)));
-    const double wr = w * ri;
+    const double r2 = fma(da, da, fma(db, db, dc * dc));
     if constexpr (MODE == kNearColloc) {
-        f[0] += wr;
+        f[0] = add_inv_root(w, r2, f[0]);
     } else if constexpr (MODE == kNearEval) {
-        const double w3 = wr * (ri * ri);
-        f[0] += wr;
+        const double w3 = inv_cube_phi(w, r2, f[0]);
         f[1] = fma(w3, da, f[1]);
         f[2] = fma(w3, db, f[2]);
         f[3] = fma(w3, dc, f[3]);
     } else {
+        const double ri = rsqrt64(r2);
+        const double wr = w * ri;
         const double ri2 = ri * ri, w3 = wr * ri2, w5 = w3 * ri2;
         const double ua = w5 * da, ub = w5 * db, uc = w5 * dc;
         f[0] += w3;
@@ -1533,7 +1633,7 @@ __device__ __forceinline__ void leaf_add(int kind, const NearGeom& g, double p1,
             near_terms<MODE>(w, da, db, qz, f);
         }
     }
-    const double h2 = h * h;
+    const double h2 = near_scale<MODE>() * (h * h);
     constexpr int NS = MODE == kNearGrad ? 7 : (MODE == kNearColloc ? 1 : 4);
 #pragma unroll
     for (int c = 0; c < NS; ++c) acc[c] = fma(h2, f[c], acc[c]);
@@ -1772,8 +1872,10 @@ __device__ void heavy_pair(const NearArgs& a, unsigned long long w, uint64_t* fr
 
 // MODE: kNearEval (phi, E at field points), kNearColloc (phi at centroids, several density
 // vectors), kNearGrad (field gradient at field points; NaN for a point on its element).
+// The depth-first variant is held to four wavefronts per SIMD (128 registers): its workgroups
+// then fit beside another stream's running far kernel (left alone the compiler takes 157).
 template <int MODE, bool DEEP>
-__global__ __launch_bounds__(kBlock) void near_kernel(NearArgs a)
+__global__ __launch_bounds__(kBlock, DEEP ? 1 : 4) void near_kernel(NearArgs a)
 {
     // the walks: the leading entries of the order (the points lying on their element follow);
     // the first `heavy` of them have deep subdivisions (DEEP: walked breadth first, a wavefront
