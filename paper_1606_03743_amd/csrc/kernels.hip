@@ -40,15 +40,6 @@ constexpr int kMaxTileElems = 64;
 
 __device__ __forceinline__ int tile_elems(int nn) { return nn >= 16 ? kTileNodes / nn : kMaxTileElems; }
 
-// 1/sqrt(x) in FP64: hardware estimate (~24 bits) refined by one third-order step
-// y (1 + e/2 + 3 e^2 / 8), e = 1 - x y^2 (relative error ~ e^3).
-__device__ __forceinline__ double rsqrt64(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-(x * y), y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
 __device__ __forceinline__ float rsqrt32(float x) { return __builtin_amdgcn_rsqf(x); }
 
 // Negative half powers in FP64, x^(-P/2) / kappa: with the hardware estimate y (~24 bits) and
@@ -63,6 +54,7 @@ __device__ __forceinline__ float rsqrt32(float x) { return __builtin_amdgcn_rsqf
 template <int P> struct HalfPower;
 template <> struct HalfPower<1> { static constexpr double kHalf = 0x1.aaaaaaaaaaaacp+0, kRest = 0x1.1c71c71c71c71p+1, kappa = 0.375; };
 template <> struct HalfPower<3> { static constexpr double kHalf = 0x1.6666666666666p+0, kRest = 0x1.7e4b17e4b17e6p-2, kappa = 1.875; };
+template <> struct HalfPower<5> { static constexpr double kHalf = 0x1.4924924924926p+0, kRest = 0x1.2cee3c9aa517ap-3, kappa = 4.375; };
 
 // The factors y^P and (e + h)^2 + c of x^(-P/2) / kappa for P = 3.
 __device__ __forceinline__ void half_power3(double x, double& y3, double& m)
@@ -85,6 +77,22 @@ __device__ __forceinline__ float inv_cube(float x)
 {
     const float y = rsqrt32(x);
     return (y * y) * y;
+}
+
+// w x^(-5/2) over half_power_scale<5, T>
+__device__ __forceinline__ double inv_fifth(double w, double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double y2 = y * y;
+    const double t = fma(-x, y2, HalfPower<5>::kHalf);
+    const double m = fma(t, t, HalfPower<5>::kRest);
+    return ((w * y) * (y2 * y2)) * m;
+}
+__device__ __forceinline__ float inv_fifth(float w, float x)
+{
+    const float y = rsqrt32(x);
+    const float y2 = y * y;
+    return (w * y) * (y2 * y2);
 }
 
 // acc + w x^(-1/2) / kappa in FP64 (w = 1: one instruction less)
@@ -255,12 +263,11 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
 // root of r^2 / w^2 is w/r itself, and (w/r)^3 times the staged values gives the three
 // field sums, which saves the multiplication by the weight per node.
 //
-// Rows form (the 7 x 7 Gauss-Legendre rectangle rule, and the gradient): the point is
+// Rows form (potential and field of the 7 x 7 Gauss-Legendre rectangle rule): the point is
 // rotated into the frame, p = (f1.d, f2.d, f3.d).  For rectangles f1 runs along the second
 // side, so the nodes of a tensor Gauss-Legendre rule that share their first coordinate share
-// b: (p2 - b)^2 + p3^2 is formed once per group of seven and r^2 takes one difference and
-// one FMA per node.  The local field (sum w (p1 - a)/r^3, sum w (p2 - b)/r^3, p3 sum w/r^3)
-// is rotated back with the frame.
+// b, and are summed in rows (pair_row).  The local field (sum w (p1 - a)/r^3, sum w (p2 - b)/r^3,
+// p3 sum w/r^3) is rotated back with the frame.
 enum FrameForm { kFrExp = 0, kFrRows = 1 };
 
 template <bool MIXED, int NRHS>
@@ -269,7 +276,7 @@ struct TileLds {
     using T4 = typename std::conditional<MIXED, float4, double4>::type;
     T4 nd[kTileNodes];  // (a, b, a^2 + b^2, w), or divided by w^2 as (a, b, a^2 + b^2, 1) / w^2
     double cx[kMaxTileElems], cy[kMaxTileElems], cz[kMaxTileElems], thr2[kMaxTileElems];
-    T fr[9][kMaxTileElems];      // point rotation: expanded -2 f1, -2 f2; rows f1, f2, f3
+    T fr[9][kMaxTileElems];      // point rotation: expanded -2 f1, -2 f2 (gradient: f1, f2); rows f1, f2, f3
     double qr[9][kMaxTileElems]; // rotation back scaled by the charge: expanded -q f1, -q f2;
                                  // rows q f1, q f2, q f3
     double q[NRHS][kMaxTileElems];
@@ -311,7 +318,7 @@ __device__ __forceinline__ TriForms fixed_forms(int nn)
 // with x_{6-j} = -x_j, the same weight for j and 6 - j and x_3 = 0.  Four slots per row:
 //   header (b, a0, w of the middle node, a0^2 + b^2), then per pair j = 0, 1, 2 with
 //   s = x_{6-j} alpha: (s, s^2, w, w s).
-// Folded (FP64): 1 / w^2 in place of w in the header, and per pair (s, s^2, 1, 0) / w^2.
+// Folded (FP64 field and potential): 1 / w^2 in place of w in the header, and per pair (s, s^2, 1, 0) / w^2.
 constexpr int kPairRowSlots = 28;
 template <bool FOLDED>
 __device__ __forceinline__ double4 pair_row_slot(const RuleTables& R, int prow, int m, double gamma, double beta,
@@ -344,7 +351,9 @@ __device__ __forceinline__ double4 pair_row_slot(const RuleTables& R, int prow, 
 // Triangles: centroid and S21 nodes (TriForms, folded nodes only) are staged as
 // (0, 0, 1/w^2, 0) and (s, |n|^2, 1, 0) / w^2 with n = s u_k.  The charges are staged times
 // scale (the constant that the node sums leave out, half_power_scale).
-template <bool TRI, bool MIXED, int NRHS, int FR, bool QR>
+// GRAD (the gradient's sums): nothing is folded; the first nfold nodes are those of a rule whose
+// orbits are known, the centroid and S21 nodes staged as (0, 0, 0, w) and (s, |n|^2, s^2, w).
+template <bool TRI, bool MIXED, int NRHS, int FR, bool QR, bool GRAD>
 __device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elements& el, const RuleTables& R, int nn,
                                            int64_t t0, int te, int rhs0, int nrhs, int nfold, int prow,
                                            const TriForms& tf, double scale)
@@ -363,7 +372,7 @@ __device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elemen
 #pragma unroll
             for (int c = 0; c < 6; ++c) {
                 const double f = el.frame[(int64_t)c * ne + e];
-                s.fr[c][k] = (T)(-2.0 * f);
+                s.fr[c][k] = (T)(GRAD ? f : -2.0 * f);
                 if (QR) s.qr[c][k] = -q * f;
                 if (TRI) s.lc[c][k] = (T)el.loc[(int64_t)c * ne + e];
             }
@@ -382,7 +391,7 @@ __device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elemen
         const int64_t e = t0 + j;
         if (!TRI && i >= prow) {
             if (i - prow < kPairRowSlots) {
-                const double4 v = pair_row_slot<!MIXED>(R, prow, i - prow, el.loc[e], el.loc[ne + e], el.loc[2 * ne + e]);
+                const double4 v = pair_row_slot<!MIXED && !GRAD>(R, prow, i - prow, el.loc[e], el.loc[ne + e], el.loc[2 * ne + e]);
                 if constexpr (MIXED) s.nd[k] = make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
                 else s.nd[k] = v;
             }
@@ -400,7 +409,7 @@ __device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elemen
                     if (q < tf.nlev && i >= tf.off[q]) { off_l = tf.off[q]; nc_l = tf.nc[q]; n21_l = tf.n21[q]; }
                 const int il = i - off_l;
                 if (il < nc_l + n21_l) {
-                    const double iw2 = 1.0 / (w * w);
+                    const double iw2 = GRAD ? 1.0 : 1.0 / (w * w);
                     double v0 = 0.0, v1 = 0.0;
                     if (il >= nc_l) {  // S21: the distinct coordinate at vertex kk
                         const int kk = (il - nc_l) % 3;
@@ -411,8 +420,9 @@ __device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elemen
                         v0 = sv * iw2;
                         v1 = fma(na, na, nb * nb) * iw2;
                     }
-                    if constexpr (MIXED) s.nd[k] = make_float4((float)v0, (float)v1, (float)iw2, 0.0f);
-                    else s.nd[k] = make_double4(v0, v1, iw2, 0.0);
+                    const double v2 = GRAD ? v0 * v0 : iw2, v3 = GRAD ? w : 0.0;
+                    if constexpr (MIXED) s.nd[k] = make_float4((float)v0, (float)v1, (float)v2, (float)v3);
+                    else s.nd[k] = make_double4(v0, v1, v2, v3);
                     continue;
                 }
             }
@@ -425,7 +435,7 @@ __device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elemen
             b = x * el.loc[ne + e];
         }
         double g = fma(a, a, b * b);
-        if (i < nfold) {
+        if (!GRAD && i < nfold) {
             const double iw2 = 1.0 / (w * w);
             a *= iw2;
             b *= iw2;
@@ -446,14 +456,15 @@ enum FarMode { kFarField = 0, kFarGrad = 1, kFarPhi = 2 };
 template <int MODE>
 struct Sums {
     static constexpr int kOut = MODE == kFarGrad ? 6 : (MODE == kFarField ? 4 : 1);   // outputs per point
-    static constexpr int kNode = MODE == kFarGrad ? 7 : (MODE == kFarField ? 4 : 1);  // element sums per point
+    static constexpr int kNode = MODE == kFarGrad ? 6 : (MODE == kFarField ? 4 : 1);  // element sums per point
 };
 
 // The constant left out of the node sums, multiplied into the staged charges (half_power_scale).
 template <int MODE, typename T>
 constexpr double sum_scale()
 {
-    return MODE == kFarGrad ? 1.0 : (MODE == kFarField ? half_power_scale<3, T>() : half_power_scale<1, T>());
+    return MODE == kFarGrad ? half_power_scale<5, T>()
+                            : (MODE == kFarField ? half_power_scale<3, T>() : half_power_scale<1, T>());
 }
 
 // Field points of one lane and their FP64 accumulators.
@@ -469,7 +480,8 @@ struct PointSet {
 template <int PPT, typename T>
 struct Local {
     T q1[PPT], q2[PPT], H[PPT];           // expanded: -2 f1.d, -2 f2.d, D^2
-    T p1[PPT], p2[PPT], p3[PPT], h[PPT];  // rows: f1.d, f2.d, f3.d, p3^2
+    T p1[PPT], p2[PPT], p3[PPT];          // rows: f1.d, f2.d, f3.d
+    T ri0[PPT], t[PPT];                   // FP32 gradient: 1/D and 1/D^2 (q1, q2 are times 1/D^2)
     double dx[PPT], dy[PPT], dz[PPT];     // d = P - centroid (FP64)
 };
 
@@ -495,10 +507,6 @@ __device__ __forceinline__ void for_nodes(int n, Term term)
     }
     for (; i < n; ++i) term(i);
 }
-
-// 1/sqrt(x) in the precision of T (FP64 refined, see rsqrt64)
-__device__ __forceinline__ double rsqrtT(double x) { return rsqrt64(x); }
-__device__ __forceinline__ float rsqrtT(float x) { return rsqrt32(x); }
 
 // One folded node of the field (r^2 / w^2 = x): returns (w/r)^3 and adds w/r to phi.  FP64: both
 // from x^(-3/2) alone, since (w/r)^3 x = w/r: 13 FP64 instructions per expanded node instead of
@@ -538,12 +546,20 @@ __device__ __forceinline__ float inv_cube_phi(float w, float x, float& phi)
 //   kFarField, expanded: (sum w/r, sum w a/r^3, sum w b/r^3, sum w/r^3);
 //              FOLD: the staged node is (a, b, g, 1) / w^2 and rsqrt(r^2 / w^2) = w/r;
 //   kFarPhi,   expanded: sum w/r;
-//   kFarGrad   (differences da = p1 - a, db = p2 - b): FP64 (sum w/r^3, sum w/r^5,
-//              sum w da/r^5, sum w db/r^5, sum w da^2/r^5, sum w db^2/r^5, sum w da db/r^5),
-//              turned into the local tensor after the loop; FP32: the local tensor itself,
-//              sum w/r^3 and sum w u_i u_j / r^3 over the unit offset u = (da, db, p3)/r (xx,
-//              yy, zz, xy, xz, yz), so that no power of 1/r above the third is formed in
-//              single precision.
+//   kFarGrad,  unfolded: (S5 = sum w/r^5, Sa = sum w a/r^5, Sb = sum w b/r^5, sum w a^2/r^5,
+//              sum w a b/r^5, sum w (a^2 + b^2)/r^5), from which add_element forms the tensor and
+//              sum w/r^3 once per pair: 17 instructions per node beside the reciprocal
+//              square root, 22 with the node's own offsets and both powers (far kernel, 15,000
+//              points x 150,000 elements, 33-point / 7 x 7, FP64: 73.0 -> 53.9 ms; mixed, 50,001 x
+//              18,000: 17.8 -> 11.9 ms).  FP32: r^2 is taken
+//              over D^2 (grad_base), so that no power of a length above the square appears in
+//              single precision, whatever the geometry's unit.
+template <int PPT, typename T>
+__device__ __forceinline__ T grad_base(const Local<PPT, T>& L, int k, T g)  // D^2 + g, or over D^2
+{
+    if constexpr (std::is_same<T, double>::value) return L.H[k] + g;
+    else return fma(L.t[k], g, T(1));
+}
 template <int PPT, int MODE, bool FOLD, typename T, typename T4>
 __device__ __forceinline__ void node_term(const T4 Q, const Local<PPT, T>& L, T (&o)[Sums<MODE>::kNode][PPT])
 {
@@ -552,37 +568,19 @@ __device__ __forceinline__ void node_term(const T4 Q, const Local<PPT, T>& L, T 
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
         if constexpr (MODE == kFarGrad) {
-            const T da = L.p1[k] - a, db = L.p2[k] - b;
-            const T ri = rsqrtT(fma(da, da, fma(db, db, L.h[k])));
-            if constexpr (F64) {
-                const T ri2 = ri * ri;
-                const T w3 = (w * ri) * ri2;
-                const T w5 = w3 * ri2;
-                const T ua = w5 * da, ub = w5 * db;
-                o[0][k] += w3;
-                o[1][k] += w5;
-                o[2][k] += ua;
-                o[3][k] += ub;
-                o[4][k] = fma(ua, da, o[4][k]);
-                o[5][k] = fma(ub, db, o[5][k]);
-                o[6][k] = fma(ua, db, o[6][k]);
-            } else {
-                const T w3 = (w * ri) * (ri * ri);
-                const T va = da * ri, vb = db * ri, vc = L.p3[k] * ri;
-                const T ua = w3 * va, ub = w3 * vb, uc = w3 * vc;
-                o[0][k] += w3;
-                o[1][k] = fma(ua, va, o[1][k]);
-                o[2][k] = fma(ub, vb, o[2][k]);
-                o[3][k] = fma(uc, vc, o[3][k]);
-                o[4][k] = fma(ua, vb, o[4][k]);
-                o[5][k] = fma(ua, vc, o[5][k]);
-                o[6][k] = fma(ub, vc, o[6][k]);
-            }
+            const T w5 = inv_fifth(w, fma(L.q1[k], a, fma(L.q2[k], b, grad_base(L, k, g))));
+            const T ua = w5 * a;
+            o[0][k] += w5;
+            o[1][k] += ua;
+            o[2][k] = fma(w5, b, o[2][k]);
+            o[3][k] = fma(ua, a, o[3][k]);
+            o[4][k] = fma(ua, b, o[4][k]);
+            o[5][k] = fma(w5, g, o[5][k]);
         } else if constexpr (FOLD) {
             const T x = fma(L.q1[k], a, fma(L.q2[k], b, fma(L.H[k], w, g)));  // r^2 / w^2
             if constexpr (MODE == kFarPhi) {
                 if constexpr (F64) o[0][k] = add_inv_root(x, o[0][k]);
-                else o[0][k] += rsqrtT(x);
+                else o[0][k] += rsqrt32(x);
             } else {
                 const T wr3 = inv_cube_phi(x, o[0][k]);
                 o[1][k] = fma(wr3, a, o[1][k]);
@@ -593,7 +591,7 @@ __device__ __forceinline__ void node_term(const T4 Q, const Local<PPT, T>& L, T 
             const T x = fma(L.q1[k], a, fma(L.q2[k], b, L.H[k] + g));
             if constexpr (MODE == kFarPhi) {
                 if constexpr (F64) o[0][k] = add_inv_root(w, x, o[0][k]);
-                else o[0][k] = fma(w, rsqrtT(x), o[0][k]);
+                else o[0][k] = fma(w, rsqrt32(x), o[0][k]);
             } else {
                 const T w3 = inv_cube_phi(w, x, o[0][k]);
                 o[1][k] = fma(w3, a, o[1][k]);
@@ -602,78 +600,6 @@ __device__ __forceinline__ void node_term(const T4 Q, const Local<PPT, T>& L, T 
             }
         }
     }
-}
-
-// Tensor rule in G groups of G nodes with the same b: per group the lane forms db and
-// (p2 - b)^2 + p3^2 once; per node one difference remains.  Field: the b-component and
-// sum w/r^3 are gathered per group.  Gradient (the FP64 sums of node_term): sum w/r^5 and
-// sum w da/r^5 are gathered per group, and the sums with db follow from them.  The sums
-// in o start at -0.0.
-template <int G, int PPT, int MODE, typename T, typename T4>
-__device__ __forceinline__ void group_body(const T4* t, int n0, const Local<PPT, T>& L, T (&o)[Sums<MODE>::kNode][PPT])
-{
-    const T b = t[n0].y;
-    T db[PPT], B[PPT], sg[PPT], xg[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        db[k] = L.p2[k] - b;
-        B[k] = fma(db[k], db[k], L.h[k]);
-        sg[k] = T(-0.0);
-        xg[k] = T(-0.0);
-    }
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-        const T a = t[n0 + i].x, w = t[n0 + i].w;
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const T da = L.p1[k] - a;
-            const T ri = rsqrtT(fma(da, da, B[k]));
-            if constexpr (MODE == kFarPhi) {
-                o[0][k] = fma(w, ri, o[0][k]);
-            } else if constexpr (MODE == kFarField) {
-                const T wr = w * ri;
-                const T w3 = wr * (ri * ri);
-                o[0][k] += wr;
-                o[1][k] = fma(w3, da, o[1][k]);
-                sg[k] += w3;
-            } else {
-                const T ri2 = ri * ri;
-                const T w3 = (w * ri) * ri2;
-                const T w5 = w3 * ri2;
-                const T ua = w5 * da;
-                o[0][k] += w3;
-                sg[k] += w5;
-                xg[k] += ua;
-                o[4][k] = fma(ua, da, o[4][k]);
-            }
-        }
-    }
-    if constexpr (MODE == kFarField) {
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            o[2][k] = fma(sg[k], db[k], o[2][k]);
-            o[3][k] += sg[k];
-        }
-    } else if constexpr (MODE == kFarGrad) {
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const T u = sg[k] * db[k];  // sum w db / r^5 of the group
-            o[1][k] += sg[k];
-            o[2][k] += xg[k];
-            o[3][k] += u;
-            o[5][k] = fma(u, db[k], o[5][k]);
-            o[6][k] = fma(xg[k], db[k], o[6][k]);
-        }
-    }
-}
-
-template <int G, int PPT, int MODE, typename T, typename T4>
-__device__ __forceinline__ void group_sum(const T4* t, int base, const Local<PPT, T>& L, T (&o)[Sums<MODE>::kNode][PPT])
-{
-    static_assert(!(MODE == kFarGrad && std::is_same<T, float>::value), "the FP32 gradient takes the node form");
-    group_body<G, PPT, MODE>(t, base, L, o);  // the first group starts the sums
-#pragma unroll 1
-    for (int g = 1; g < G; ++g) group_body<G, PPT, MODE>(t, base + g * G, L, o);
 }
 
 // One pair row of the 7 x 7 rule (slots n0 .. n0 + 3, see pair_row_slot) for potential and
@@ -708,11 +634,11 @@ __device__ __forceinline__ void pair_row(const T4* t, int n0, const Local<PPT, T
     for (int k = 0; k < PPT; ++k) {
         if constexpr (MODE == kFarPhi) {
             if constexpr (F64) o[0][k] = add_inv_root(C[k] * wc, o[0][k]);
-            else o[0][k] = fma(wc, rsqrtT(C[k]), o[0][k]);
+            else o[0][k] = fma(wc, rsqrt32(C[k]), o[0][k]);
         } else if constexpr (F64) {
             sg[k] = inv_cube(C[k] * wc) * wc;
         } else {
-            const T ri = rsqrtT(C[k]);
+            const T ri = rsqrt32(C[k]);
             o[0][k] = fma(wc, ri, o[0][k]);
             sg[k] = wc * ((ri * ri) * ri);
         }
@@ -739,7 +665,7 @@ __device__ __forceinline__ void pair_row(const T4* t, int n0, const Local<PPT, T
             } else {
                 const T u = C[k] + s2;
                 const T xp = fma(mq[k], sv, u), xm = fma(-mq[k], sv, u);
-                const T rp = rsqrtT(xp), rm = rsqrtT(xm);
+                const T rp = rsqrt32(xp), rm = rsqrt32(xm);
                 o[0][k] = fma(w, rp + rm, o[0][k]);
                 if constexpr (MODE == kFarField) {
                     const T r3p = (rp * rp) * rp, r3m = (rm * rm) * rm;
@@ -780,6 +706,109 @@ __device__ __forceinline__ void pair_rows_sum(const T4* t, int base, const Local
     }
 }
 
+// One pair row for the gradient's sums (node_term, kFarGrad): with s5, s1, s2 the row's sums of
+// w/r^5 times 1, the offset a - a0 and its square, the row adds s5, a0 s5 + s1, b s5,
+// a0^2 s5 + 2 a0 s1 + s2, b (a0 s5 + s1) and the squares' sum.  12 instructions per node beside
+// the reciprocal square root (16 with each node's own offset).  FP32 over D^2, as in node_term.
+template <int PPT, typename T, typename T4>
+__device__ __forceinline__ void grad_pair_row(const T4* t, int n0, const Local<PPT, T>& L, T (&o)[6][PPT])
+{
+    constexpr bool F64 = std::is_same<T, double>::value;
+    const T4 hd = t[n0];
+    const T b = hd.x, a0 = hd.y, wc = hd.z, g0 = hd.w;
+    T C[PPT], mq[PPT], s5[PPT], s1[PPT], s2[PPT];
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+        C[k] = fma(L.q1[k], a0, fma(L.q2[k], b, grad_base(L, k, g0)));
+        mq[k] = fma(T(2), F64 ? a0 : a0 * L.t[k], L.q1[k]);  // -2 (p1 - a0), over D^2 in FP32
+        s5[k] = inv_fifth(wc, C[k]);
+    }
+#pragma unroll
+    for (int pi = 1; pi <= 3; ++pi) {
+        const T4 Q = t[n0 + pi];
+        const T sv = Q.x, sq = Q.y, w = Q.z;
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            const T u = F64 ? C[k] + sq : fma(L.t[k], sq, C[k]);
+            const T wp = inv_fifth(w, fma(mq[k], sv, u)), wm = inv_fifth(w, fma(-mq[k], sv, u));
+            const T sum = wp + wm, dif = wp - wm;
+            s5[k] += sum;
+            s1[k] = pi == 1 ? sv * dif : fma(sv, dif, s1[k]);
+            s2[k] = pi == 1 ? sq * sum : fma(sq, sum, s2[k]);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+        const T ra = fma(a0, s5[k], s1[k]), rb = b * s5[k], raa = fma(a0, ra + s1[k], s2[k]);
+        o[0][k] += s5[k];
+        o[1][k] += ra;
+        o[2][k] += rb;
+        o[3][k] += raa;
+        o[4][k] = fma(b, ra, o[4][k]);
+        o[5][k] = fma(b, rb, o[5][k] + raa);
+    }
+}
+
+// A compiled triangle rule with its orbit structure for the gradient's sums: on the S21 orbits
+// per vertex T = sum w s/r^5 and Q = sum w s^2/r^5 (12 instructions per node beside the reciprocal
+// square root), turned into the in-plane sums with the vertex u_k before the other orbits add.
+template <int NN, int PPT, typename Lds, typename T>
+__device__ __forceinline__ void tri_grad_sum(const Lds& s, int j, int base, const Local<PPT, T>& L, T (&o)[6][PPT])
+{
+    using O = TriOrbits<NN>;
+    constexpr int NC = O::nc, N21 = O::n21, GS = O::gs, NG = NN - NC - 3 * N21;
+    if constexpr (NC > 0) {
+        const T w = s.nd[base].w;
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) o[0][k] += inv_fifth(w, grad_base(L, k, T(0)));
+    }
+    if constexpr (N21 > 0) {
+        const T u[3][2] = { { s.lc[0][j], s.lc[1][j] }, { s.lc[2][j], s.lc[3][j] }, { s.lc[4][j], s.lc[5][j] } };
+        T Pk[3][PPT], Tk[3][PPT], Qk[3][PPT];
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            Pk[0][k] = fma(u[0][0], L.q1[k], u[0][1] * L.q2[k]);
+            Pk[1][k] = fma(u[1][0], L.q1[k], u[1][1] * L.q2[k]);
+            Pk[2][k] = -(Pk[0][k] + Pk[1][k]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) Tk[c][k] = Qk[c][k] = T(-0.0);
+        }
+#pragma unroll 1
+        for (int ob = 0; ob < N21; ++ob) {
+#pragma unroll
+            for (int kk = 0; kk < 3; ++kk) {
+                const auto Q = s.nd[base + NC + 3 * ob + kk];  // (s, |n|^2, s^2, w)
+#pragma unroll
+                for (int k = 0; k < PPT; ++k) {
+                    const T w5 = inv_fifth(Q.w, fma(Q.x, Pk[kk][k], grad_base(L, k, Q.y)));
+                    o[0][k] += w5;
+                    Tk[kk][k] = fma(w5, Q.x, Tk[kk][k]);
+                    Qk[kk][k] = fma(w5, Q.z, Qk[kk][k]);
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < PPT; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const T ta = u[c][0] * Qk[c][k], tb = u[c][1] * Qk[c][k];
+                o[1][k] = fma(u[c][0], Tk[c][k], o[1][k]);
+                o[2][k] = fma(u[c][1], Tk[c][k], o[2][k]);
+                o[3][k] = fma(u[c][0], ta, o[3][k]);
+                o[4][k] = fma(u[c][1], ta, o[4][k]);
+                o[5][k] = fma(u[c][0], ta, fma(u[c][1], tb, o[5][k]));
+            }
+    }
+    if constexpr (NG > 0) {
+        const int g0 = base + NC + 3 * N21;
+#pragma unroll 1
+        for (int g = 0; g < NG / GS; ++g) {
+#pragma unroll
+            for (int u = 0; u < GS; ++u) node_term<PPT, kFarGrad, false>(s.nd[g0 + g * GS + u], L, o);
+        }
+    }
+}
+
 // One folded node whose r^2 / w^2 is x: potential (and field sums S3 and, for S21 nodes, the
 // vertex sum tv = sum (w/r)^3 s / w^2, from which S1 and S2 follow per pair).
 template <int MODE, typename T>
@@ -787,7 +816,7 @@ __device__ __forceinline__ void folded_point(T x, T iw2, T sv, T& o0, T& o3, T& 
 {
     if constexpr (MODE == kFarPhi) {
         if constexpr (std::is_same<T, double>::value) o0 = add_inv_root(x, o0);
-        else o0 += rsqrtT(x);
+        else o0 += rsqrt32(x);
     } else {
         const T wr3 = inv_cube_phi(x, o0);
         tv = fma(wr3, sv, tv);
@@ -864,56 +893,40 @@ __device__ __forceinline__ void tri_sum(const Lds& s, int j, int base, const Loc
 // charge) in the precision T of the tile (FP64, or FP32 for the mixed path).  NN > 0:
 // compile-time node count; G > 0: tensor rule in groups of G (rows form).  Field, expanded:
 // (sum w/r, S1, S2, S3) in node coordinates; rows: (sum w/r, local E1, local E2 without p3,
-// sum w/r^3).  Gradient: the local tensor (sum w/r^3; sum w d_i d_j / r^5 for xx, yy, zz,
-// xy, xz, yz, d = (da, db, p3)).
+// sum w/r^3).  Gradient: the six sums of node_term.
 template <int NN, int G, bool FOLD, bool TRI, int PPT, int MODE, typename Lds, typename T>
 __device__ __forceinline__ void element_sum(const Lds& s, int j, int base, int n, const Local<PPT, T>& L,
                                             T (&o)[Sums<MODE>::kNode][PPT])
 {
     constexpr int S = Sums<MODE>::kNode;
-    constexpr bool MIXED = std::is_same<T, float>::value;
 #pragma unroll
     for (int c = 0; c < S; ++c)
 #pragma unroll
         for (int k = 0; k < PPT; ++k) o[c][k] = T(-0.0);
     const int nn = NN > 0 ? NN : n;
-    constexpr bool GROUPS = G > 0 && (MODE != kFarGrad || !MIXED);
-    if constexpr (GROUPS && MODE == kFarGrad) {
-        group_sum<G, PPT, MODE>(s.nd, base, L, o);
-    } else if constexpr (GROUPS) {
+    if constexpr (G > 0) {
         static_assert(G == 7, "pair rows are built for the 7 x 7 rule");
-        pair_rows_sum<PPT, MODE>(s.nd, base, L, o);
-    } else if constexpr (TRI && FOLD && NN > 0 && MODE != kFarGrad) {
+        if constexpr (MODE == kFarGrad) {
+#pragma unroll 1
+            for (int r = 0; r < 7; ++r) grad_pair_row<PPT>(s.nd, base + 4 * r, L, o);
+        } else {
+            pair_rows_sum<PPT, MODE>(s.nd, base, L, o);
+        }
+    } else if constexpr (TRI && NN > 0 && MODE == kFarGrad) {
+        tri_grad_sum<NN, PPT>(s, j, base, L, o);
+    } else if constexpr (TRI && FOLD && NN > 0) {
         tri_sum<NN, PPT, MODE>(s, j, base, L, o);
     } else {
         node_term<PPT, MODE, FOLD>(s.nd[base], L, o);
         for_nodes<NN>(nn, [&](int i) { node_term<PPT, MODE, FOLD>(s.nd[base + i], L, o); });
     }
-    if constexpr (MODE == kFarGrad && !MIXED) {
-        T r[S][PPT];
-#pragma unroll
-        for (int c = 0; c < S; ++c)
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) r[c][k] = o[c][k];
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            o[0][k] = r[0][k];
-            o[1][k] = r[4][k];
-            o[2][k] = r[5][k];
-            o[3][k] = L.h[k] * r[1][k];
-            o[4][k] = r[6][k];
-            o[5][k] = L.p3[k] * r[2][k];
-            o[6][k] = L.p3[k] * r[3][k];
-        }
-    }
 }
 
 // Offsets of the lane's points from element j of the tile: D^2 in FP64 (the distance test,
 // Sec. 2) and the coordinates the node sums need, in their precision.  Expanded: -2 f1.d,
-// -2 f2.d and |p|^2 = D^2 (the rotation keeps the length, to rounding); rows: p = F d and
-// p3^2; BOTH (rectangles with the rule chosen by distance ratio): rows, and the expanded
-// coordinates from them.
-template <int FR, bool BOTH, int PPT, typename Lds, typename T>
+// -2 f2.d and |p|^2 = D^2 (the rotation keeps the length, to rounding); rows: p = F d, and the
+// expanded coordinates from them.  GRAD: in FP32 also 1/D and 1/D^2, and -2p over D^2 (grad_base).
+template <int FR, bool GRAD, int PPT, typename Lds, typename T>
 __device__ __forceinline__ void to_frame(const Lds& s, int j, const double (&x)[PPT], const double (&y)[PPT],
                                          const double (&z)[PPT], double (&D2)[PPT], Local<PPT, T>& L)
 {
@@ -926,20 +939,26 @@ __device__ __forceinline__ void to_frame(const Lds& s, int j, const double (&x)[
         L.dz[k] = dz;
         D2[k] = fma(dx, dx, fma(dy, dy, dz * dz));
         const T u = (T)dx, v = (T)dy, w = (T)dz;
+        L.H[k] = (T)D2[k];
         if constexpr (FR == kFrExp) {
             L.q1[k] = fma(u, s.fr[0][j], fma(v, s.fr[1][j], w * s.fr[2][j]));
             L.q2[k] = fma(u, s.fr[3][j], fma(v, s.fr[4][j], w * s.fr[5][j]));
-            L.H[k] = (T)D2[k];
+            if constexpr (GRAD) {
+                T f = T(-2);
+                if constexpr (std::is_same<T, float>::value) {
+                    L.ri0[k] = rsqrt32(L.H[k]);
+                    L.t[k] = L.ri0[k] * L.ri0[k];
+                    f *= L.t[k];
+                }
+                L.q1[k] *= f;
+                L.q2[k] *= f;
+            }
         } else {
             L.p1[k] = fma(u, s.fr[0][j], fma(v, s.fr[1][j], w * s.fr[2][j]));
             L.p2[k] = fma(u, s.fr[3][j], fma(v, s.fr[4][j], w * s.fr[5][j]));
             L.p3[k] = fma(u, s.fr[6][j], fma(v, s.fr[7][j], w * s.fr[8][j]));
-            L.h[k] = L.p3[k] * L.p3[k];
-            if constexpr (BOTH) {
-                L.q1[k] = T(-2) * L.p1[k];
-                L.q2[k] = T(-2) * L.p2[k];
-                L.H[k] = (T)D2[k];
-            }
+            L.q1[k] = T(-2) * L.p1[k];
+            L.q2[k] = T(-2) * L.p2[k];
         }
     }
 }
@@ -947,8 +966,11 @@ __device__ __forceinline__ void to_frame(const Lds& s, int j, const double (&x)[
 // acc += the element's contribution to point k (charge q, sums o), in FP64.
 //   expanded sums:  phi += q sum w/r;  E += (q S3) d - (q f1) S1 - (q f2) S2;
 //   rows:           phi += q sum w/r;  E += (q f1) E1 + (q f2) E2 + (q f3) p3 S3;
-//   gradient:       the global tensor M = F m F^T of the local one m (F: the frame vectors
-//                   as columns), dE_i/dx_j += q (delta_ij sum w/r^3 - 3 M_ij).
+//   gradient:       dE_i/dx_j += q (delta_ij sum w/r^3 - 3 M_ij) with M = sum w (d - n)(d - n)^T / r^5
+//                   over the nodes n = a f1 + b f2: M_ij = d_i z_j - v_i d_j + N_ij, v = Sa f1 + Sb f2,
+//                   z = S5 d - v, N the in-plane second moments; sum w/r^3 from r^2 = D^2 + q1 a + q2 b +
+//                   a^2 + b^2.  About 45 instructions per pair; rotating a local tensor takes twice
+//                   that.  FP32: over D (d, v) and D^2 (N), the charge carrying 1/D^3.
 template <int FR, int PPT, int MODE, typename Lds, typename T>
 __device__ __forceinline__ void add_element(PointSet<PPT, MODE>& P, int k, double q, const Lds& s, int j,
                                             const Local<PPT, T>& L, const T (&o)[Sums<MODE>::kNode][PPT])
@@ -967,21 +989,35 @@ __device__ __forceinline__ void add_element(PointSet<PPT, MODE>& P, int k, doubl
                 P.acc[1 + c][k] = fma(s.qr[c][j], e1, fma(s.qr[3 + c][j], e2, fma(s.qr[6 + c][j], e3, P.acc[1 + c][k])));
         }
     } else {
-        const T m[3][3] = { { o[1][k], o[4][k], o[5][k] },
-                            { o[4][k], o[2][k], o[6][k] },
-                            { o[5][k], o[6][k], o[3][k] } };
-        T U[3][3];  // U[a][c] = sum_b m[a][b] f_b[c]
+        T S5 = o[0][k], Sa = o[1][k], Sb = o[2][k], Saa = o[3][k], Sab = o[4][k], Sg = o[5][k];
+        T d[3] = { (T)L.dx[k], (T)L.dy[k], (T)L.dz[k] };
+        T s3;
+        if constexpr (std::is_same<T, double>::value) {
+            s3 = fma(L.H[k], S5, fma(L.q1[k], Sa, fma(L.q2[k], Sb, Sg)));
+        } else {
+            const T ri0 = L.ri0[k], t = L.t[k];
+            Sg *= t;
+            s3 = S5 + fma(L.q1[k], Sa, fma(L.q2[k], Sb, Sg));
+            Sa *= ri0; Sb *= ri0; Saa *= t; Sab *= t;
+            d[0] *= ri0; d[1] *= ri0; d[2] *= ri0;
+            q *= (double)(ri0 * t);
+        }
+        const T Sbb = Sg - Saa;
+        T v[3], z[3], g1[3], g2[3], f1[3], f2[3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                U[a][c] = fma(m[a][0], s.fr[c][j], fma(m[a][1], s.fr[3 + c][j], m[a][2] * s.fr[6 + c][j]));
-        auto M = [&](int u, int v) -> double {
-            return (double)fma(s.fr[u][j], U[0][v], fma(s.fr[3 + u][j], U[1][v], s.fr[6 + u][j] * U[2][v]));
+        for (int c = 0; c < 3; ++c) {
+            f1[c] = s.fr[c][j];
+            f2[c] = s.fr[3 + c][j];
+            v[c] = fma(f1[c], Sa, f2[c] * Sb);
+            z[c] = fma(S5, d[c], -v[c]);
+            g1[c] = fma(f1[c], Saa, f2[c] * Sab);
+            g2[c] = fma(f1[c], Sab, f2[c] * Sbb);
+        }
+        auto M = [&](int u, int w) -> double {
+            return (double)fma(d[u], z[w], fma(-v[u], d[w], fma(f1[u], g1[w], f2[u] * g2[w])));
         };
-        const double s3 = (double)o[0][k];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) P.acc[c][k] = fma(q, fma(-3.0, M(c, c), s3), P.acc[c][k]);
+        for (int c = 0; c < 3; ++c) P.acc[c][k] = fma(q, fma(-3.0, M(c, c), (double)s3), P.acc[c][k]);
         P.acc[3][k] = fma(-3.0 * q, M(0, 1), P.acc[3][k]);
         P.acc[4][k] = fma(-3.0 * q, M(0, 2), P.acc[4][k]);
         P.acc[5][k] = fma(-3.0 * q, M(1, 2), P.acc[5][k]);
@@ -994,7 +1030,7 @@ constexpr int tensor_group() { return (!TRI && NN == 49) ? 7 : 0; }
 
 // frame form of an element kind with a compiled rule of NN nodes
 template <bool TRI, int NN, int MODE>
-constexpr int frame_form() { return (MODE == kFarGrad || tensor_group<TRI, NN>() > 0) ? kFrRows : kFrExp; }
+constexpr int frame_form() { return (MODE != kFarGrad && tensor_group<TRI, NN>() > 0) ? kFrRows : kFrExp; }
 
 // One element kind over [e_begin, e_end) with one rule; NN > 0 is the compile-time node
 // count, NN == 0 reads it at run time.  FOLD: the rule's weights are all positive (the
@@ -1005,22 +1041,24 @@ __device__ __forceinline__ void far_eval_range(const FarArgs& a, Lds& s, PointSe
 {
     using T = typename Lds::T;
     constexpr int FR = frame_form<TRI, NN, MODE>();
-    constexpr bool FOLD_ = FOLD && FR == kFrExp;
+    constexpr bool GRAD = MODE == kFarGrad;
+    constexpr bool FOLD_ = FOLD && FR == kFrExp && !GRAD;
+    constexpr bool ORBITS = FOLD_ || (GRAD && TRI && NN > 0);
     const int nn = NN > 0 ? NN : (TRI ? a.rules.nt : a.rules.nr);
     const int TE = tile_elems(nn);
-    const TriForms tf = fixed_forms<NN, TRI && FOLD_>(nn);
+    const TriForms tf = fixed_forms<NN, TRI && ORBITS>(nn);
     for (int64_t t0 = e_begin; t0 < e_end; t0 += TE) {
         const int te = (int)min((int64_t)TE, e_end - t0);
         __syncthreads();
-        constexpr bool PROWS = tensor_group<TRI, NN>() > 0 && MODE != kFarGrad;
-        stage_tile<TRI, MIXED, 1, FR, MODE == kFarField>(s, a.el, a.rules, nn, t0, te, a.rhs, 1, FOLD_ ? nn : 0,
-                                                         PROWS ? 0 : nn, tf, sum_scale<MODE, T>());
+        stage_tile<TRI, MIXED, 1, FR, MODE == kFarField, GRAD>(s, a.el, a.rules, nn, t0, te, a.rhs, 1,
+                                                               ORBITS ? nn : 0, tensor_group<TRI, NN>() > 0 ? 0 : nn,
+                                                               tf, sum_scale<MODE, T>());
         __syncthreads();
         for (int j = 0; j < te; ++j) {
             const double thr2 = s.thr2[j], q = s.q[0][j];
             double D2[PPT];
             Local<PPT, T> L;
-            to_frame<FR, FR == kFrRows && MODE != kFarGrad>(s, j, P.x, P.y, P.z, D2, L);
+            to_frame<FR, GRAD>(s, j, P.x, P.y, P.z, D2, L);
             bool nr[PPT];
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
@@ -1076,7 +1114,7 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
 {
     using T = typename Lds::T;
     constexpr bool GRAD = MODE == kFarGrad;
-    constexpr int FR = (TRI && !GRAD) ? kFrExp : kFrRows;
+    constexpr int FR = (TRI || GRAD) ? kFrExp : kFrRows;
     constexpr bool FOLD = N0 > 0 && !GRAD;
     const int* off = TRI ? a.lv.tri_off : a.lv.rect_off;
     const double* c = TRI ? a.lv.tri_c : a.lv.rect_c;
@@ -1084,7 +1122,7 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
     const double c0 = c[0], c1 = c[1], c2 = c[2];
     const int TE = tile_elems(nn);
     TriForms tf{ 4, { off[0], o1, o2, o3, nn }, { 0, 0, 0, 0 }, { 0, 0, 0, 0 } };
-    if (TRI && FOLD) {
+    if (TRI && N0 > 0) {
         tf.nc[0] = TriOrbits<N0>::nc; tf.n21[0] = 3 * TriOrbits<N0>::n21;
         tf.nc[1] = TriOrbits<N1>::nc; tf.n21[1] = 3 * TriOrbits<N1>::n21;
         tf.nc[2] = TriOrbits<N2>::nc; tf.n21[2] = 3 * TriOrbits<N2>::n21;
@@ -1100,16 +1138,16 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
         unsigned w0 = 0, w1 = 0, w2 = 0, w3 = 0, nc = 0, n0 = 0, n1 = 0, n2 = 0;
         __syncthreads();
         // the 7 x 7 last level of the rectangles keeps its weights (rows form)
-        const int nfold = !FOLD ? 0 : (tensor_group<TRI, N3>() > 0 ? o3 : nn);
-        const int prow = (tensor_group<TRI, N3>() > 0 && !GRAD) ? o3 : nn;
-        stage_tile<TRI, MIXED, 1, FR, !GRAD>(s, a.el, a.lv.tab, nn, t0, te, a.rhs, 1, nfold, prow, tf,
+        const int nfold = N0 == 0 ? 0 : (tensor_group<TRI, N3>() > 0 ? o3 : nn);
+        const int prow = tensor_group<TRI, N3>() > 0 ? o3 : nn;
+        stage_tile<TRI, MIXED, 1, FR, !GRAD, GRAD>(s, a.el, a.lv.tab, nn, t0, te, a.rhs, 1, nfold, prow, tf,
                                              sum_scale<MODE, T>());
         __syncthreads();
         for (int j = 0; j < te; ++j) {
             const double thr2 = s.thr2[j], q = s.q[0][j];
             double D2[PPT];
             Local<PPT, T> L;
-            to_frame<FR, !TRI && !GRAD>(s, j, P.x, P.y, P.z, D2, L);
+            to_frame<FR, GRAD>(s, j, P.x, P.y, P.z, D2, L);
             // the level each pair's distance ratio asks for, as wavefront masks straight from the
             // comparisons: pairs for which level 0 suffices, then level 1, level 2, and every far
             // pair (near pairs are listed by near_list_kernel and contribute nothing here); the
@@ -1162,10 +1200,8 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
 // DR == false: one rule per kind, NT / NR nodes.  DR == true: levels (T0..T3 / R0..R3).
 // GRAD: field gradient instead of potential and field.  Compiled node counts (NT, NR > 0)
 // are used only for rules whose weights are all positive (their nodes are folded).
-// The FP64 gradient with levels is held to three wavefronts per SIMD (167 registers, a few
-// bytes of spill): left alone the compiler takes 220 and runs two, 3.6 % slower.
 template <bool DR, int NT, int NR, int T1, int T2, int T3, int R1, int R2, int R3, bool MIXED, int PPT, bool GRAD>
-__global__ __launch_bounds__(kBlock, (DR && GRAD && !MIXED) ? 3 : 1) void far_eval_kernel(FarArgs a)
+__global__ __launch_bounds__(kBlock) void far_eval_kernel(FarArgs a)
 {
     constexpr int MODE = GRAD ? kFarGrad : kFarField;
     constexpr int NO = Sums<MODE>::kOut;
@@ -1244,14 +1280,14 @@ __device__ __forceinline__ void far_colloc_range(const FarArgs& a, Lds& s, const
     for (int64_t t0 = e_begin; t0 < e_end; t0 += TE) {
         const int te = (int)min((int64_t)TE, e_end - t0);
         __syncthreads();
-        stage_tile<TRI, MIXED, kMaxRhs, FR, false>(s, a.el, a.rules, nn, t0, te, 0, nrhs, FOLD ? nn : 0,
+        stage_tile<TRI, MIXED, kMaxRhs, FR, false, false>(s, a.el, a.rules, nn, t0, te, 0, nrhs, FOLD ? nn : 0,
                                                    tensor_group<TRI, NN>() > 0 ? 0 : nn, tf, sum_scale<kFarPhi, T>());
         __syncthreads();
         for (int j = 0; j < te; ++j) {
             const double thr2 = s.thr2[j];
             double D2[PPT];
             Local<PPT, T> L;
-            to_frame<FR, FR == kFrRows>(s, j, px, py, pz, D2, L);
+            to_frame<FR, false>(s, j, px, py, pz, D2, L);
             bool nr[PPT];
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
@@ -1432,14 +1468,15 @@ __device__ __forceinline__ void node_geometry(const NearState& s, const NearGeom
 }
 
 // Sums of one Gaussian point at offsets (da, db, dc) in the element's frame, weight w (unit
-// element charge; the field's and the potential's lack the factor near_scale):
+// element charge, without the factor near_scale):
 //   field:        f0 += w/r, (f1, f2, f3) += w (da, db, dc)/r^3;
 //   collocation:  f0 += w/r;
 //   gradient:     f0 += w/r^3, (f1 .. f6) += w (da^2, db^2, dc^2, da db, da dc, db dc)/r^5.
 template <int MODE>
 constexpr double near_scale()
 {
-    return MODE == kNearColloc ? HalfPower<1>::kappa : (MODE == kNearEval ? HalfPower<3>::kappa : 1.0);
+    return MODE == kNearColloc ? HalfPower<1>::kappa
+                               : (MODE == kNearEval ? HalfPower<3>::kappa : HalfPower<5>::kappa);
 }
 template <int MODE>
 __device__ __forceinline__ void near_terms(double w, double da, double db, double dc, double (&f)[7])
@@ -1453,11 +1490,9 @@ __device__ __forceinline__ void near_terms(double w, double da, double db, doubl
         f[2] = fma(w3, db, f[2]);
         f[3] = fma(w3, dc, f[3]);
     } else {
-        const double ri = rsqrt64(r2);
-        const double wr = w * ri;
-        const double ri2 = ri * ri, w3 = wr * ri2, w5 = w3 * ri2;
+        const double w5 = inv_fifth(w, r2);
         const double ua = w5 * da, ub = w5 * db, uc = w5 * dc;
-        f[0] += w3;
+        f[0] = fma(w5, r2, f[0]);  // w/r^3
         f[1] = fma(ua, da, f[1]);
         f[2] = fma(ub, db, f[2]);
         f[3] = fma(uc, dc, f[3]);
@@ -2090,13 +2125,13 @@ hipError_t far_eval_dispatch(const FarArgs& a, hipStream_t s)
 }
 
 // Gradient: compile-time node counts for the default rules only; one point per lane for
-// those in the mixed path (7 % faster than two on the 150k-element cylinder; FP64 is
-// fastest with two).
+// those (FP64, 15,000 points x 150,000 elements: far kernel 53.9 ms, 56.6 ms with two; mixed the
+// same with one and two), two with the levels (52.3 ms, 53.3 ms with one).
 template <bool MIXED>
 hipError_t far_grad_dispatch(const FarArgs& a, hipStream_t s)
 {
     constexpr int PPT = 2;
-    constexpr int PPT_LONG = MIXED ? 1 : 2;
+    constexpr int PPT_LONG = 1;
     if (a.dr_rules) {
         const int* t = a.lv.tri_off;
         const int* r = a.lv.rect_off;
