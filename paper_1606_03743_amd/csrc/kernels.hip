@@ -10,20 +10,21 @@
 //                      the rule chosen by distance ratio; field or field gradient.
 //  far_colloc_kernel   the same sum, potential only, at element centroids, for up to eight
 //                      density vectors (matrix-free collocation product).
-//  near_kernel         FP64 near field over the dense list: each lane walks the recursive
-//                      subdivision of its pair depth first (triangle: four midpoint
-//                      children; rectangle: 2 x 2) using lattice coordinates instead of a
-//                      stack; a child at DR >= near_dr of its own (or at the depth cap) gets
-//                      the element's rule.  Lanes take pairs from a shared cursor, the most
+//  near_kernel         FP64 near field over the dense list: each pair's recursive subdivision
+//                      (triangle: four midpoint children; rectangle: 2 x 2) is walked in lattice
+//                      coordinates; a child at DR >= near_dr of its own (or at the depth cap) gets
+//                      the element's rule.  Deep pairs, and all pairs of a short list, are walked
+//                      breadth first by a wavefront each; the others one per lane depth first,
+//                      64 leaves at a time taking the rule together.  Pairs are handed out the most
 //                      expensive first (near_order.hip).  Each pair's result goes to its
 //                      own slot in (point, element) order; the per-point sums are formed in
 //                      that order afterwards (near_order.hip), so results are reproducible
 //                      bit for bit.
 //                      Pairs whose point lies on the element (found by the cost pass, last in
 //                      the order) get the exact polar integral, one lane per pair, after the
-//                      walk loop: kept out of the loop so that the walk's register footprint
-//                      stays near 128 VGPRs, and its workgroups fit beside the far kernels of
-//                      other streams.
+//                      walk loop: kept out of the loop so that the depth-first walk's register
+//                      footprint stays below 128 VGPRs, and its workgroups fit beside the far
+//                      kernels of other streams.
 #include "bemc_internal.h"
 #include "on_element.h"
 
@@ -133,33 +134,130 @@ __device__ __forceinline__ unsigned long long bcast_u64(unsigned long long v, in
     return ((unsigned long long)hi << 32) | lo;
 }
 
-// Wavefront-level compaction of near pairs: one atomic per wavefront, lane offsets by
-// popcount.  Called with every lane of the wavefront active.
-__device__ __forceinline__ void record_near(bool is_near, uint32_t p, uint32_t e, NearPair* list,
-                                            unsigned long long cap, DevCounters* ctr)
+// v of one lane, the same in every lane (a scalar)
+__device__ __forceinline__ double read_lane(double v, int lane)
 {
-    const unsigned long long m = lane_mask(is_near);
-    if (m == 0ull) return;
-    const int first = __ffsll((long long)m) - 1;
-    unsigned long long base = 0;
-    if (lane_id() == first) base = atomicAdd(&ctr->near_count, (unsigned long long)__popcll(m));
-    base = bcast_u64(base, first);
-    if (is_near) {
-        const unsigned long long pos = base + lanes_below(m);
-        if (pos < cap) list[pos] = NearPair{ p, e };
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, lane), hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// LDS written by some lanes of a wavefront, read by others: finish the writes first.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Near pairs of one wavefront on their way to the list: compacted into a buffer of its own in
+// LDS (lane offsets by popcount), which goes to the list with one atomic on the list's length
+// when another 64 pairs might not fit.  Appending each candidate's pairs with an atomic of its
+// own bound the pass: they all hit one address (32,768 points x 150,000 elements, 697,000 pairs:
+// see near_list_kernel).  Called with every lane of the wavefront active.
+constexpr unsigned kListBuf = 512;
+struct NearBuffer {
+    NearPair* buf;  // [kListBuf]
+    unsigned n;     // pairs held (the same in every lane)
+
+    __device__ __forceinline__ void flush(NearPair* list, unsigned long long cap, DevCounters* ctr)
+    {
+        if (n == 0) return;
+        wave_lds_sync();
+        unsigned long long base = 0;
+        if (lane_id() == 0) base = atomicAdd(&ctr->near_count, (unsigned long long)n);
+        base = bcast_u64(base, 0);
+        for (unsigned i = lane_id(); i < n; i += 64)
+            if (base + i < cap) list[base + i] = buf[i];
+        wave_lds_sync();
+        n = 0;
+    }
+    __device__ __forceinline__ void record(bool is_near, uint32_t p, uint32_t e, NearPair* list,
+                                           unsigned long long cap, DevCounters* ctr)
+    {
+        const unsigned long long m = lane_mask(is_near);
+        if (m == 0ull) return;
+        if (is_near) buf[n + lanes_below(m)] = NearPair{ p, e };
+        n += (unsigned)__popcll(m);
+        if (n > kListBuf - 64) flush(list, cap, ctr);
+    }
+};
+
+// ------------------------------------------------------------- near-pair list -----
+// An axis-aligned box: low and high corner.
+struct Box {
+    double lo[3], hi[3];
+
+    // is a centroid within its threshold t2 = (near_dr L)^2 of the box?  (an empty box: no)
+    __device__ __forceinline__ bool in_reach(double cx, double cy, double cz, double t2) const
+    {
+        const double dx = fmax(fmax(lo[0] - cx, cx - hi[0]), 0.0);
+        const double dy = fmax(fmax(lo[1] - cy, cy - hi[1]), 0.0);
+        const double dz = fmax(fmax(lo[2] - cz, cz - hi[2]), 0.0);
+        return fma(dx, dx, fma(dy, dy, dz * dz)) < t2;
+    }
+};
+
+// One axis of split_boxes: the least and greatest of the lanes up to this one (pl, ph) and of the
+// later ones (sl, sh).
+__device__ __forceinline__ void split_axis(double lo, double hi, double& pl, double& ph, double& sl, double& sh)
+{
+    const int lane = lane_id();
+    pl = sl = lo;
+    ph = sh = hi;
+    for (int o = 1; o < 64; o <<= 1) {
+        const double a = __shfl_up(pl, o), b = __shfl_up(ph, o), c = __shfl_down(sl, o), d = __shfl_down(sh, o);
+        if (lane >= o) { pl = fmin(pl, a); ph = fmax(ph, b); }
+        if (lane + o < 64) { sl = fmin(sl, c); sh = fmax(sh, d); }
+    }
+    sl = __shfl_down(sl, 1);
+    sh = __shfl_down(sh, 1);
+    if (lane == 63) { sl = INFINITY; sh = -INFINITY; }
+}
+
+// Two boxes for the wavefront's points (one per lane; an invalid lane's is empty): the points up
+// to a lane and those after it, where their edges add up to least.  (The axes are scanned twice,
+// one at a time: keeping all three takes 60 registers more.)
+__device__ __forceinline__ void split_boxes(const Box& own, Box& a, Box& b)
+{
+    double cost = 0.0, pl, ph, sl, sh;
+#pragma unroll 1
+    for (int c = 0; c < 3; ++c) {
+        const double lo = c == 0 ? own.lo[0] : (c == 1 ? own.lo[1] : own.lo[2]);
+        const double hi = c == 0 ? own.hi[0] : (c == 1 ? own.hi[1] : own.hi[2]);
+        split_axis(lo, hi, pl, ph, sl, sh);
+        cost += fmax(ph - pl, 0.0) + fmax(sh - sl, 0.0);
+    }
+    double least = cost;
+    for (int o = 32; o > 0; o >>= 1) least = fmin(least, __shfl_xor(least, o));
+    const unsigned long long at = lane_mask(cost == least);
+    const int split = at ? (int)__builtin_ctzll(at) : 63;  // (no lane: coordinates that are not numbers)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        split_axis(own.lo[c], own.hi[c], pl, ph, sl, sh);
+        a.lo[c] = read_lane(pl, split);  // (scalar registers: the boxes stay live to the end)
+        a.hi[c] = read_lane(ph, split);
+        b.lo[c] = read_lane(sl, split);
+        b.hi[c] = read_lane(sh, split);
     }
 }
 
-// ------------------------------------------------------------- near-pair list -----
 // Every (point, element) pair with D^2 < (near_dr L)^2 (the distance-ratio switch, Sec. 2)
-// goes into the near-pair list, compacted per wavefront; pairs past the capacity are
+// goes into the near-pair list, compacted per wavefront (NearBuffer); pairs past the capacity are
 // counted, not stored.  A workgroup takes kListPoints consecutive points (Morton order:
 // neighbours in space) and one chunk of the elements (more chunks when the points are few),
-// and bounds the points by a box; an element takes the per-point test only when its
-// centroid lies within near_dr L of that box.  Collocation: the points are the centroids
+// and bounds the points by a box; the elements whose centroid lies within near_dr L of that box
+// are its candidates, kept in LDS, and 64 consecutive points take the per-point test of a candidate
+// only when it passes the same test with their own boxes (64 candidates at a time, one per lane).
+// There are two boxes for them: a run of points across a step of the Morton curve spans the
+// whole geometry, and the few such runs set the pass's time; split where the two parts' boxes
+// are smallest, both are small.  With the buffered appends: 131,071 points x 150,000 elements
+// 6.2 -> 0.57 ms (2.3 with one box), 32,768 points 3.0 -> 0.43 ms; 777 points x 3,600 elements 220 ->
+// 23 us; 50,000 centroids 4.3 -> 0.42 ms.  Collocation: the points are the centroids
 // themselves (the same [3][n] layout).
 constexpr int kListPPT = 2;
 constexpr int kListPoints = kBlock * kListPPT;
+constexpr int64_t kListFine = 1024;  // elements of a chunk from which the points' own boxes pay
 
 __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restrict__ pts, int64_t n, Elements el,
                                                            NearPair* __restrict__ list, unsigned long long cap,
@@ -170,14 +268,18 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
     __shared__ uint32_t cand[kBlock];
     __shared__ double4 cand_c[kBlock];  // the candidates' centroids and thresholds
     __shared__ int ncand;
+    __shared__ NearPair pairs[kBlock / 64][kListBuf];
     const int64_t ne = el.ne;
     double x[kListPPT], y[kListPPT], z[kListPPT];
     bool valid[kListPPT];
     uint32_t idx[kListPPT];
     double lo[3] = { INFINITY, INFINITY, INFINITY }, hi[3] = { -INFINITY, -INFINITY, -INFINITY };
+    // a short chunk's candidates are tested at once: forming the boxes takes longer (30 us)
+    const bool fine = chunk > kListFine;
+    Box part[kListPPT][2];
 #pragma unroll
     for (int k = 0; k < kListPPT; ++k) {
-        const int64_t p = (int64_t)blockIdx.x * kListPoints + (int64_t)k * kBlock + threadIdx.x;
+        const int64_t p = (int64_t)blockIdx.x * kListPoints + (threadIdx.x / 64) * (64 * kListPPT) + k * 64 + lane_id();
         valid[k] = p < n;
         idx[k] = (uint32_t)p;
         x[k] = valid[k] ? pts[p] : 0.0;
@@ -186,6 +288,11 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
         if (valid[k]) {
             lo[0] = fmin(lo[0], x[k]); lo[1] = fmin(lo[1], y[k]); lo[2] = fmin(lo[2], z[k]);
             hi[0] = fmax(hi[0], x[k]); hi[1] = fmax(hi[1], y[k]); hi[2] = fmax(hi[2], z[k]);
+        }
+        if (fine) {
+            const double e0 = valid[k] ? 0.0 : INFINITY;
+            split_boxes(Box{ { x[k] + e0, y[k] + e0, z[k] + e0 }, { x[k] - e0, y[k] - e0, z[k] - e0 } }, part[k][0],
+                        part[k][1]);
         }
     }
 #pragma unroll
@@ -207,7 +314,8 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
         box[threadIdx.x] = v;
     }
     __syncthreads();
-    const double b0 = box[0], b1 = box[1], b2 = box[2], b3 = box[3], b4 = box[4], b5 = box[5];
+    NearBuffer near{ pairs[wave], 0u };
+    const Box all{ { box[0], box[1], box[2] }, { box[3], box[4], box[5] } };
     // this workgroup's chunk of the elements (blockIdx.y)
     const int64_t e_begin = (int64_t)blockIdx.y * chunk, e_end = min(ne, e_begin + chunk);
     for (int64_t c0 = e_begin; c0 < e_end; c0 += kBlock) {
@@ -216,10 +324,7 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
         double cx = 0.0, cy = 0.0, cz = 0.0, t2 = 0.0;
         if (e < e_end) {
             cx = el.cen[e]; cy = el.cen[ne + e]; cz = el.cen[2 * ne + e]; t2 = el.thr2[e];
-            const double dx = fmax(fmax(b0 - cx, cx - b3), 0.0);
-            const double dy = fmax(fmax(b1 - cy, cy - b4), 0.0);
-            const double dz = fmax(fmax(b2 - cz, cz - b5), 0.0);
-            hit = fma(dx, dx, fma(dy, dy, dz * dz)) < t2;
+            hit = all.in_reach(cx, cy, cz, t2);
         }
         const unsigned long long m = lane_mask(hit);
         if (m) {
@@ -233,21 +338,29 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
         }
         __syncthreads();
         const int nc = ncand;
-        for (int i = 0; i < nc; ++i) {
-            const uint32_t ce = cand[i];
-            const double4 cc = cand_c[i];  // one LDS read for the whole wavefront
-            const double cx = cc.x, cy = cc.y, cz = cc.z, t2 = cc.w;
+        for (int i0 = 0; i0 < nc; i0 += 64) {
+            bool mine[kListPPT] = {};
+            if (i0 + lane_id() < nc) {
+                const double4 cc = cand_c[i0 + lane_id()];
 #pragma unroll
-            for (int k = 0; k < kListPPT; ++k) {
-                const double dx = x[k] - cx, dy = y[k] - cy, dz = z[k] - cz;
-                const bool nr = valid[k] && fma(dx, dx, fma(dy, dy, dz * dz)) < t2;
-                record_near(nr, idx[k], ce, list, cap, ctr);
+                for (int k = 0; k < kListPPT; ++k)
+                    mine[k] = !fine || part[k][0].in_reach(cc.x, cc.y, cc.z, cc.w) || part[k][1].in_reach(cc.x, cc.y, cc.z, cc.w);
             }
+#pragma unroll
+            for (int k = 0; k < kListPPT; ++k)
+                for (unsigned long long todo = lane_mask(mine[k]); todo; todo &= todo - 1) {
+                    const int i = i0 + __ffsll((long long)todo) - 1;
+                    const double4 cc = cand_c[i];  // one LDS read for the whole wavefront
+                    const double dx = x[k] - cc.x, dy = y[k] - cc.y, dz = z[k] - cc.z;
+                    const bool nr = valid[k] && fma(dx, dx, fma(dy, dy, dz * dz)) < cc.w;
+                    near.record(nr, idx[k], cand[i], list, cap, ctr);
+                }
         }
         __syncthreads();
         if (threadIdx.x == 0) ncand = 0;
         __syncthreads();
     }
+    near.flush(list, cap, ctr);
 }
 
 // ---------------------------------------------------------------- LDS staging ------
@@ -1479,6 +1592,8 @@ constexpr double near_scale()
                                : (MODE == kNearEval ? HalfPower<3>::kappa : HalfPower<5>::kappa);
 }
 template <int MODE>
+constexpr int near_sums() { return MODE == kNearGrad ? 7 : (MODE == kNearColloc ? 1 : 4); }
+template <int MODE>
 __device__ __forceinline__ void near_terms(double w, double da, double db, double dc, double (&f)[7])
 {
     const double r2 = fma(da, da, fma(db, db, dc * dc));
@@ -1575,10 +1690,26 @@ __device__ __forceinline__ void on_element_pairs(const NearArgs& a, unsigned lon
     if (n_on) atomicAdd(&a.ctr->on_surface, n_on);
 }
 
+// A list of at most this many pairs is walked a wavefront per pair, breadth first, whatever the pairs'
+// depth: fewer than eight pairs per resident wavefront, the lanes' walks would leave most of the
+// chip idle (4,100 pairs: near stage 0.23 ms, 0.40 ms with the shallow pairs one per lane; 40,000:
+// 0.71 and 0.55 ms; 250,000: 2.5 and 0.7 ms).
+constexpr unsigned long long kShortList = 32768;
 constexpr unsigned kNearWindow = 64;  // entries of the order a wavefront claims at a time
 constexpr int kNearWaves = kBlock / 64;
 constexpr int kFront = 128;  // near nodes of one level of a breadth-first walk (per wavefront)
 constexpr int kLeafQ = 128;  // leaves waiting for the rule: a batch of 64 and one chunk's more
+constexpr unsigned kFrontUp = 1u << 31;  // orientation of a node in the near levels' stores
+
+// One wavefront's share of LDS in the near kernel.
+template <int NS>
+struct NearLdsT {
+    uint2 front[2][kFront];         // breadth-first walk: a level's near nodes, the next level's
+    uint2 pos[kLeafQ];              // queued leaves
+    uint16_t meta[kLeafQ];
+    unsigned long long round[64];   // the lanes that queued a leaf, per round of a batch
+    double res[NS][64];             // the batch's leaf sums
+};
 
 // A pair's walk set-up from the element's record: the element kind, its node geometry in the
 // element's frame, the field point in that frame (offset from the centroid: numbers of the
@@ -1638,17 +1769,18 @@ __device__ __forceinline__ bool visit_node(const NearState& s, const NearGeom& g
 }
 
 // The element's rule on leaf node nd (scale h), weights scaled by the area ratio h^2, added to
-// acc (the sums of near_terms in the element's frame).
+// acc (the sums of near_terms in the element's frame); only the rule's nodes first, first + step, ...
 template <int MODE>
 __device__ __forceinline__ void leaf_add(int kind, const NearGeom& g, double p1, double p2, double p3,
                                          const NodeGeom& nd, double h, const double4* __restrict__ tri_nodes,
-                                         const double4* __restrict__ rect_nodes, int nt, int nr, double (&acc)[7])
+                                         const double4* __restrict__ rect_nodes, int nt, int nr, double (&acc)[7],
+                                         int first = 0, int step = 1)
 {
     double f[7] = { 0, 0, 0, 0, 0, 0, 0 };
     if (kind == 0) {
         const double q1 = p1 - nd.x0, q2 = p2 - nd.y0, q3 = p3 - nd.z0;
 #pragma unroll 4
-        for (int i = 0; i < nt; ++i) {
+        for (int i = first; i < nt; i += step) {
             const double4 q = tri_nodes[i];
             const double lb = q.y, lc = q.z, w = q.w;
             const double da = fma(-lb, nd.w1x, fma(-lc, nd.w2x, q1));
@@ -1660,7 +1792,7 @@ __device__ __forceinline__ void leaf_add(int kind, const NearGeom& g, double p1,
         const double qx = p1 - nd.cx, qy = p2 - nd.cy, qz = p3 - nd.cz;
         const double H1x = h * (0.5 * g.ux), H1y = h * (0.5 * g.uy), H2x = h * (0.5 * g.vx);
 #pragma unroll 4
-        for (int i = 0; i < nr; ++i) {
+        for (int i = first; i < nr; i += step) {
             const double4 q = rect_nodes[i];
             const double x = q.x, y = q.y, w = q.z;
             const double da = fma(-x, H1x, fma(-y, H2x, qx));
@@ -1669,9 +1801,8 @@ __device__ __forceinline__ void leaf_add(int kind, const NearGeom& g, double p1,
         }
     }
     const double h2 = near_scale<MODE>() * (h * h);
-    constexpr int NS = MODE == kNearGrad ? 7 : (MODE == kNearColloc ? 1 : 4);
 #pragma unroll
-    for (int c = 0; c < NS; ++c) acc[c] = fma(h2, f[c], acc[c]);
+    for (int c = 0; c < near_sums<MODE>(); ++c) acc[c] = fma(h2, f[c], acc[c]);
 }
 
 // The pair's own result record at its slot (32 bytes for the field, 48 for the gradient);
@@ -1718,30 +1849,16 @@ __device__ __forceinline__ void write_record(const NearArgs& a, uint32_t e, unsi
     }
 }
 
-// A node of a breadth-first walk in one 64-bit word: i, j (24 bits each: depth cap <= 24),
-// orientation, level.
-__device__ __forceinline__ uint64_t pack_node(const NearState& s)
+// A node of a walk kept in LDS: its lattice position (i, j < 2^30), and a word with its level, its
+// orientation and (one wavefront's queue of several pairs) the lane whose pair it belongs to.
+__device__ __forceinline__ uint2 node_pos(const NearState& s) { return make_uint2((unsigned)s.i, (unsigned)s.j); }
+__device__ __forceinline__ uint16_t node_meta(const NearState& s, int lane)
 {
-    return (uint64_t)(uint32_t)s.i | ((uint64_t)(uint32_t)s.j << 24) | ((uint64_t)(s.up ? 1 : 0) << 48) |
-           ((uint64_t)(uint32_t)s.level << 49);
+    return (uint16_t)(s.level | (s.up ? 32 : 0) | (lane << 6));
 }
-__device__ __forceinline__ NearState unpack_node(uint64_t v, int kind)
+__device__ __forceinline__ NearState unpack_node(uint2 pos, unsigned meta, int kind)
 {
-    NearState s;
-    s.kind = kind;
-    s.i = (int)(v & 0xffffffull);
-    s.j = (int)((v >> 24) & 0xffffffull);
-    s.up = ((v >> 48) & 1ull) != 0;
-    s.level = (int)(v >> 49);
-    return s;
-}
-
-// LDS written by some lanes of a wavefront, read by others: finish the writes first.
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    return NearState{ kind, (int)(meta & 31u), (int)pos.x, (int)pos.y, (meta & 32u) != 0 };
 }
 
 // Move to the next node of a depth-first walk of the subtree below `root` (level) after
@@ -1783,8 +1900,8 @@ __device__ void walk_subtree(NearState s, const NearGeom& g, double p1, double p
     }
 }
 
-// A pair with a deep subdivision (the leading cost classes), walked by a whole wavefront
-// breadth first: per level, the children of the level's near nodes are tested 64 at a time,
+// A pair with a deep subdivision (the leading cost classes; every pair of a short list), walked by
+// a whole wavefront breadth first: per level, the children of the level's near nodes are tested 64 at a time,
 // the near ones (above the depth cap) form the next level, the others are leaves; leaves
 // wait in LDS until 64 of them can take the rule loop together, one per lane.  A point very
 // close to an element has a near region of some 65 nodes at every level (three node sizes
@@ -1793,12 +1910,13 @@ __device__ void walk_subtree(NearState s, const NearGeom& g, double p1, double p
 // so results are reproducible.  More near nodes in a level than kFront: the lane that found
 // one walks its subtree depth first itself.  The visit limit ends the walk after the level in
 // which the pair's visits pass it.
-template <int MODE>
-__device__ void heavy_pair(const NearArgs& a, unsigned long long w, uint64_t* front, uint64_t* leafq,
-                           const double4* __restrict__ tri_nodes, const double4* __restrict__ rect_nodes, int nt,
+template <int MODE, typename NearLds>
+__device__ void heavy_pair(const NearArgs& a, unsigned long long w, NearLds& q, const double4* __restrict__ tri_nodes, const double4* __restrict__ rect_nodes, int nt,
                            int nr, int lane, unsigned long long& n_leaves, unsigned long long& n_cap,
                            unsigned long long& n_limit, int& max_level)
 {
+    uint2* const leafq = q.pos;
+    uint16_t* const leafm = q.meta;
     const NearPair pr = a.opair[w];
     const unsigned long long cur = a.slot[a.order[w]];
     int kind;
@@ -1806,10 +1924,12 @@ __device__ void heavy_pair(const NearArgs& a, unsigned long long w, uint64_t* fr
     double p1, p2, p3, thr2;
     pair_setup<MODE>(a, pr.point, pr.elem, kind, g, p1, p2, p3, thr2);
     double acc[7] = { 0, 0, 0, 0, 0, 0, 0 };
-    // the same in every lane: the current level's near nodes (nF, in cur_f), the next level's
-    // (nN), the next child of the level to test (base), the queued leaves (nq), the visits
-    uint64_t* cur_f = front;
-    uint64_t* nxt_f = front + kFront;
+    // the same in every lane: the current level's near nodes (nF, in cur_f: positions and
+    // orientations), the next level's (nN), the next child of the level to test (base), the queued
+    // leaves (nq), the visits
+    uint2* cur_f = q.front[0];
+    uint2* nxt_f = q.front[1];
+    int level = 0;  // of the nodes in cur_f
     int nF = 1, nN = 0, base = 0, nq = 0;
     long long visits = 0;
     bool done = false;
@@ -1820,19 +1940,21 @@ __device__ void heavy_pair(const NearArgs& a, unsigned long long w, uint64_t* fr
             NodeGeom nd;
             n_leaves++;
             if (visit_node(s, g, p1, p2, p3, thr2, h, nd)) n_cap++;
-            leafq[0] = pack_node(s);
+            leafq[0] = node_pos(s);
+            leafm[0] = node_meta(s, 0);
         }
         nq = 1;
         done = true;
     } else if (lane == 0) {
-        cur_f[0] = pack_node(NearState{ kind, 0, 0, 0, true });
+        cur_f[0] = make_uint2(kFrontUp, 0u);
     }
     wave_lds_sync();
     while (true) {
         if (!done && base >= 4 * nF) {  // the level is tested: on to the next one
-            uint64_t* t = cur_f;
+            uint2* t = cur_f;
             cur_f = nxt_f;
             nxt_f = t;
+            ++level;
             nF = nN;
             nN = 0;
             base = 0;
@@ -1845,16 +1967,20 @@ __device__ void heavy_pair(const NearArgs& a, unsigned long long w, uint64_t* fr
         }
         if (nq >= 64 || (done && nq > 0)) {  // a batch of leaves, one per lane
             const int k = min(nq, 64);
-            if (lane < k) {
-                const NearState t = unpack_node(leafq[lane], kind);
+            // fewer than 33 leaves: 2, 4, ... lanes to a leaf share its rule's nodes
+            const int logk = k > 1 ? 32 - __builtin_clz((unsigned)(k - 1)) : 0;
+            const int at = lane & ((1 << logk) - 1);
+            if (at < k) {
+                const NearState t = unpack_node(leafq[at], leafm[at], kind);
                 double h;
                 NodeGeom nd;
                 (void)visit_node(t, g, p1, p2, p3, thr2, h, nd);
-                leaf_add<MODE>(kind, g, p1, p2, p3, nd, h, tri_nodes, rect_nodes, nt, nr, acc);
+                leaf_add<MODE>(kind, g, p1, p2, p3, nd, h, tri_nodes, rect_nodes, nt, nr, acc, lane >> logk, 64 >> logk);
             }
-            const uint64_t rest = lane < nq - k ? leafq[k + lane] : 0ull;
+            const uint2 rest = lane < nq - k ? leafq[k + lane] : make_uint2(0u, 0u);
+            const uint16_t restm = lane < nq - k ? leafm[k + lane] : (uint16_t)0;
             wave_lds_sync();
-            if (lane < nq - k) leafq[lane] = rest;
+            if (lane < nq - k) { leafq[lane] = rest; leafm[lane] = restm; }
             wave_lds_sync();
             nq -= k;
             continue;
@@ -1866,7 +1992,8 @@ __device__ void heavy_pair(const NearArgs& a, unsigned long long w, uint64_t* fr
         NearState s{ kind, 0, 0, 0, true };
         bool near = false;
         if (valid) {
-            s = unpack_node(cur_f[c >> 2], kind);
+            const uint2 f = cur_f[c >> 2];
+            s = NearState{ kind, level, (int)(f.x & ~kFrontUp), (int)f.y, (f.x & kFrontUp) != 0 };
             to_child(s, c & 3);
             double h;
             NodeGeom nd;
@@ -1885,11 +2012,14 @@ __device__ void heavy_pair(const NearArgs& a, unsigned long long w, uint64_t* fr
         const unsigned long long dm = lane_mask(desc);
         const int pos = nN + (int)lanes_below(dm);
         const bool spill = desc && pos >= kFront;
-        if (desc && !spill) nxt_f[pos] = pack_node(s);
+        if (desc && !spill) nxt_f[pos] = make_uint2((unsigned)s.i | (s.up ? kFrontUp : 0u), (unsigned)s.j);
         nN = min(kFront, nN + (int)__popcll(dm));
         // leaves: the queue (fewer than 64 wait when a chunk adds at most 64)
         const unsigned long long lm = lane_mask(leaf);
-        if (leaf) leafq[nq + (int)lanes_below(lm)] = pack_node(s);
+        if (leaf) {
+            leafq[nq + (int)lanes_below(lm)] = node_pos(s);
+            leafm[nq + (int)lanes_below(lm)] = node_meta(s, 0);
+        }
         nq += (int)__popcll(lm);
         base += 64;
         wave_lds_sync();
@@ -1900,7 +2030,7 @@ __device__ void heavy_pair(const NearArgs& a, unsigned long long w, uint64_t* fr
     wave_lds_sync();  // the queue and the levels are reused by the next pair
     // the lanes' sums added by a fixed butterfly (every lane ends with the same total)
 #pragma unroll
-    for (int c = 0; c < 7; ++c)
+    for (int c = 0; c < near_sums<MODE>(); ++c)
         for (int o = 32; o > 0; o >>= 1) acc[c] += __shfl_xor(acc[c], o);
     if (lane == 0) write_record<MODE>(a, pr.elem, cur, acc);
 }
@@ -1915,38 +2045,54 @@ __global__ __launch_bounds__(kBlock, DEEP ? 1 : 4) void near_kernel(NearArgs a)
     // the walks: the leading entries of the order (the points lying on their element follow);
     // the first `heavy` of them have deep subdivisions (DEEP: walked breadth first, a wavefront
     // each; else depth first like the others)
-    const unsigned long long total = *a.walk_end, heavy = DEEP ? *a.heavy_end : 0ull;
+    const unsigned long long total = *a.walk_end;
+    const unsigned long long heavy = !DEEP ? 0ull : (total <= kShortList ? total : (unsigned long long)*a.heavy_end);
     const int lane = lane_id();
     // the rules' nodes in LDS: a leaf's loop reads them at one address for the whole wavefront
     // (from global memory every node would be a vector load and a wait for it)
     extern __shared__ double4 near_rule_nodes[];  // [nt] triangle (la, lb, lc, w), [nr] rectangle (x, y, w, 0)
-    __shared__ uint64_t near_front[kNearWaves][2 * kFront];
-    __shared__ uint64_t near_leafq[kNearWaves][kLeafQ];
+    __shared__ NearLdsT<near_sums<MODE>()> near_lds[kNearWaves];
+    auto& Q = near_lds[threadIdx.x / 64];
     const int nt = a.rules.nt, nr = a.rules.nr;
-    for (int i = threadIdx.x; i < nt + nr; i += kBlock) {
-        const double* src = i < nt ? a.rules.tri + 4 * i : a.rules.rect + 4 * (i - nt);
-        near_rule_nodes[i] = make_double4(src[0], src[1], src[2], src[3]);
+    // Every wavefront's first deep pair and first window are its own by its index; the shared
+    // cursors hand out what follows.  (Claiming those too, a launch's four thousand wavefronts
+    // queue up at one address: 102 shallow pairs took 75 us, 16 us so.)
+    const unsigned long long waves = (unsigned long long)gridDim.x * kNearWaves;
+    const unsigned long long wave = (unsigned long long)blockIdx.x * kNearWaves + threadIdx.x / 64;
+    const unsigned long long first_wave = (unsigned long long)blockIdx.x * kNearWaves;
+    if (first_wave < heavy || heavy + first_wave * kNearWindow < total) {  // the workgroup has walks
+        for (int i = threadIdx.x; i < nt + nr; i += kBlock) {
+            const double* src = i < nt ? a.rules.tri + 4 * i : a.rules.rect + 4 * (i - nt);
+            near_rule_nodes[i] = make_double4(src[0], src[1], src[2], src[3]);
+        }
+        __syncthreads();
     }
-    __syncthreads();
     const double4* __restrict__ tri_nodes = near_rule_nodes;
     const double4* __restrict__ rect_nodes = near_rule_nodes + nt;
 
     unsigned long long n_leaves = 0, n_cap = 0, n_limit = 0;
     int max_level = 0;
 
-    // ---- the deep pairs, one per wavefront at a time (no claim at all without them: a
-    // launch's thousand wavefronts claiming one counter cost microseconds)
-    while (DEEP && heavy > 0) {
-        unsigned long long hw = 0;
-        if (lane == 0) hw = atomicAdd(&a.ctr->heavy_cursor, 1ull);
-        hw = bcast_u64(hw, 0);
-        if (hw >= heavy) break;
-        heavy_pair<MODE>(a, hw, near_front[threadIdx.x / 64], near_leafq[threadIdx.x / 64], tri_nodes, rect_nodes,
-                         nt, nr, lane, n_leaves, n_cap, n_limit, max_level);
+    // ---- the deep pairs, one per wavefront at a time
+    if (DEEP) {
+        for (unsigned long long hw = wave; hw < heavy;) {
+            heavy_pair<MODE>(a, hw, Q, tri_nodes, rect_nodes, nt, nr, lane, n_leaves, n_cap, n_limit, max_level);
+            if (heavy <= waves) break;
+            if (lane == 0) hw = waves + atomicAdd(&a.ctr->heavy_cursor, 1ull);
+            hw = bcast_u64(hw, 0);
+        }
     }
 
-    // ---- the other pairs, one per lane, depth first
-    bool active = false;
+    // ---- the other pairs, 64 at a time: each lane walks one depth first, but only down to its
+    // leaves, which it queues; 64 queued leaves then take the rule together, one per lane,
+    // whichever pairs they come from.  A leaf's rule costs about fifteen times the steps that find
+    // it, so a wavefront with one long walk left still works on all lanes (with the rule in the
+    // walk's own loop such walks, hundreds of leaves long, set the kernel's time).  Each pair's
+    // lane adds its leaves one after another in the order of its walk, so the sum does not depend on
+    // which other pairs share the wavefront.
+    enum { kIdle = 0, kWalking = 1, kWalked = 2, kOut = 3 };
+    int state = kIdle;
+    bool found = false, is_near = false;  // the walk stands at a leaf that is not queued yet
     NearState st{ 0, 0, 0, 0, true };
     uint32_t e = 0;
     unsigned long long cur = 0;  // result slot of the pair in hand
@@ -1957,73 +2103,155 @@ __global__ __launch_bounds__(kBlock, DEEP ? 1 : 4) void near_kernel(NearArgs a)
     // the wavefront's window of the order (the same in every lane): kNearWindow consecutive
     // entries claimed with one atomic, handed to its lanes as they need pairs; consecutive
     // entries are pairs of one cost class, so the lanes walk trees of one kind and similar size
-    unsigned long long win = 0, win_end = 0;
+    unsigned long long win = heavy + wave * kNearWindow, win_end = win + kNearWindow;
 
-    while (total > heavy) {
+    const bool more = heavy + waves * kNearWindow < total;  // windows beyond the first ones
+    for (bool go = win < total; go;) {
         // ---- refill from the window (a new window when it is used up)
-        const unsigned long long need = lane_mask(!active);
+        const unsigned long long need = lane_mask(state == kIdle);
         if (need) {
             if (win >= win_end) {
-                const int first = __ffsll((long long)need) - 1;
-                unsigned long long b = 0;
-                if (lane == first) b = atomicAdd(&a.ctr->cursor, (unsigned long long)kNearWindow);
-                win = heavy + bcast_u64(b, first);
+                win = total;
+                if (more) {
+                    const int first = __ffsll((long long)need) - 1;
+                    unsigned long long b = 0;
+                    if (lane == first) b = atomicAdd(&a.ctr->cursor, (unsigned long long)kNearWindow);
+                    win = heavy + waves * kNearWindow + bcast_u64(b, first);
+                }
                 win_end = win + kNearWindow;
             }
             const unsigned rank = lanes_below(need);
             const unsigned long long avail = win_end - win, w = win + rank;
             win += min(avail, (unsigned long long)__popcll(need));
             // a lane without an entry (the window ran out) waits for the next one
-            if (!active && rank < avail) {
-                if (w >= total) break;
-                const NearPair pr = a.opair[w];  // most expensive pairs first
-                cur = a.slot[a.order[w]];
-                e = pr.elem;
-                pair_setup<MODE>(a, pr.point, pr.elem, st.kind, g, p1, p2, p3, thr2);
+            if (state == kIdle && rank < avail) {
+                if (w >= total) {
+                    state = kOut;
+                } else {
+                    const NearPair pr = a.opair[w];  // most expensive pairs first
+                    cur = a.slot[a.order[w]];
+                    e = pr.elem;
+                    pair_setup<MODE>(a, pr.point, pr.elem, st.kind, g, p1, p2, p3, thr2);
 #pragma unroll
-                for (int c = 0; c < 7; ++c) acc[c] = 0.0;
-                visits = 0;
-                active = true;
-                st.i = 0; st.j = 0; st.up = true;
-                if (a.max_depth <= 0) st.level = 0;  // evaluate the rule on the element itself (depth cap)
-                else st.level = 1;                   // first child of the root
+                    for (int c = 0; c < 7; ++c) acc[c] = 0.0;
+                    visits = 0;
+                    state = kWalking;
+                    found = false;
+                    st.i = 0; st.j = 0; st.up = true;
+                    if (a.max_depth <= 0) st.level = 0;  // evaluate the rule on the element itself (depth cap)
+                    else st.level = 1;                   // first child of the root
+                }
             }
         }
-
-        if (!active) continue;
-        // ---- visit nodes from st down to the next leaf (each lane on its own: internal nodes
-        // cost a distance test, so the lanes then take the leaf loop together)
-        double h;
-        bool is_near;
-        NodeGeom nd;
-        while (true) {
-            is_near = visit_node(st, g, p1, p2, p3, thr2, h, nd);
-            ++visits;
-            if (st.level > max_level) max_level = st.level;
-            if (!(is_near && st.level < a.max_depth && visits <= a.visit_limit)) break;
-            to_child(st, 0);
+        // ---- queue leaves in rounds, at most one per lane and round
+        int nq = 0, rounds = 0;
+        while (nq < 64) {
+            const bool walking = state == kWalking;
+            const unsigned long long wm = lane_mask(walking);
+            if (wm == 0ull) break;
+            if (walking && !found) {  // from st down to the next leaf
+                double h;
+                NodeGeom nd;
+                while (true) {
+                    is_near = visit_node(st, g, p1, p2, p3, thr2, h, nd);
+                    ++visits;
+                    if (st.level > max_level) max_level = st.level;
+                    if (!(is_near && st.level < a.max_depth && visits <= a.visit_limit)) break;
+                    to_child(st, 0);
+                }
+                found = true;
+            }
+            const int pos = nq + (int)lanes_below(wm);
+            const bool take = walking && pos < 64;
+            const unsigned long long tm = lane_mask(take);
+            if (lane == 0) Q.round[rounds] = tm;
+            ++rounds;
+            nq += (int)__popcll(tm);
+            if (take) {
+                Q.pos[pos] = node_pos(st);
+                Q.meta[pos] = node_meta(st, lane);
+                found = false;
+                n_leaves++;
+                if (is_near) n_cap++;
+                if (visits > a.visit_limit) {
+                    n_limit++;
+                    state = kWalked;
+                } else if (!advance(st)) {
+                    state = kWalked;
+                }
+            }
         }
-        leaf_add<MODE>(st.kind, g, p1, p2, p3, nd, h, tri_nodes, rect_nodes, nt, nr, acc);
-        n_leaves++;
-        if (is_near) n_cap++;
-        bool finished;
-        if (visits > a.visit_limit) {
-            n_limit++;
-            finished = true;
-        } else {
-            finished = !advance(st);
+        if (nq == 0) {
+            go = lane_mask(state != kOut) != 0ull;
+            continue;
         }
-        if (!finished) continue;
-        write_record<MODE>(a, e, cur, acc);
-        active = false;
-        st.level = 0;
+        wave_lds_sync();
+        // ---- the rule on the queued leaves, one per lane, with their pairs' geometry
+        {
+            const int at = min(lane, nq - 1);
+            const uint2 lp = Q.pos[at];
+            const unsigned lm = Q.meta[at];
+            const int o = (int)(lm >> 6);
+            NearGeom og;
+            og.ax = __shfl(g.ax, o); og.ay = __shfl(g.ay, o); og.az = __shfl(g.az, o);
+            og.ux = __shfl(g.ux, o); og.uy = __shfl(g.uy, o); og.uz = __shfl(g.uz, o);
+            og.vx = __shfl(g.vx, o); og.vy = __shfl(g.vy, o); og.vz = __shfl(g.vz, o);
+            const double o1 = __shfl(p1, o), o2 = __shfl(p2, o), o3 = __shfl(p3, o);
+            const NearState t = unpack_node(lp, lm, __shfl(st.kind, o));
+            if (lane < nq) {
+                const double h = ldexp(1.0, -t.level);
+                NodeGeom nd;
+                node_geometry(t, og, h, nd);
+                double f[7] = { 0, 0, 0, 0, 0, 0, 0 };
+                leaf_add<MODE>(t.kind, og, o1, o2, o3, nd, h, tri_nodes, rect_nodes, nt, nr, f);
+#pragma unroll
+                for (int c = 0; c < near_sums<MODE>(); ++c) Q.res[c][lane] = f[c];
+            }
+        }
+        wave_lds_sync();
+        // ---- each pair's lane adds its leaves in the order of its walk
+        for (int r = 0, first = 0; r < rounds; ++r) {
+            const unsigned long long tm = Q.round[r];
+            if ((tm >> lane) & 1ull) {
+                const int at = first + (int)lanes_below(tm);
+#pragma unroll
+                for (int c = 0; c < near_sums<MODE>(); ++c) acc[c] += Q.res[c][at];
+            }
+            first += (int)__popcll(tm);
+        }
+        if (state == kWalked) {
+            write_record<MODE>(a, e, cur, acc);
+            state = kIdle;
+        }
+        wave_lds_sync();  // the queue is filled again
     }
 
-    // per-lane counters -> one atomic per counter per lane that has something to add
-    if (n_leaves) atomicAdd(&a.ctr->leaves, n_leaves);
-    if (n_cap) atomicAdd(&a.ctr->cap_hits, n_cap);
-    if (n_limit) atomicAdd(&a.ctr->visit_limit_hits, n_limit);
-    if (max_level) atomicMax(&a.ctr->max_depth, (unsigned long long)max_level);
+    // the lanes' counters, added up over the workgroup: one atomic per counter and workgroup (one per
+    // lane took longer than the walks of a short list: 262,000 of them at one address)
+    {
+        __shared__ unsigned long long total_of[4];
+        if (threadIdx.x < 4) total_of[threadIdx.x] = 0ull;
+        for (int o = 32; o > 0; o >>= 1) {
+            n_leaves += __shfl_xor(n_leaves, o);
+            n_cap += __shfl_xor(n_cap, o);
+            n_limit += __shfl_xor(n_limit, o);
+            max_level = max(max_level, __shfl_xor(max_level, o));
+        }
+        __syncthreads();
+        if (lane == 0 && n_leaves) {
+            atomicAdd(&total_of[0], n_leaves);
+            if (n_cap) atomicAdd(&total_of[1], n_cap);
+            if (n_limit) atomicAdd(&total_of[2], n_limit);
+            atomicMax(&total_of[3], (unsigned long long)max_level);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0 && total_of[0]) {
+            atomicAdd(&a.ctr->leaves, total_of[0]);
+            if (total_of[1]) atomicAdd(&a.ctr->cap_hits, total_of[1]);
+            if (total_of[2]) atomicAdd(&a.ctr->visit_limit_hits, total_of[2]);
+            if (total_of[3]) atomicMax(&a.ctr->max_depth, total_of[3]);
+        }
+    }
 
     // then the pairs whose point lies on the element (after the walk loop: none of its
     // state is live here, so the closed form does not add to the walk's registers)
@@ -2185,17 +2413,33 @@ hipError_t launch_far_grad(const FarArgs& a, int precision, hipStream_t s)
     return precision == 1 ? far_grad_dispatch<true>(a, s) : far_grad_dispatch<false>(a, s);
 }
 
+// Workgroups of a persistent near kernel: as many as the GPU holds at once (a workgroup beyond
+// them would start its own first pairs, the expensive ones, when the others are through), no more
+// than the list can hold pairs.  Every lane leaves once the pairs are handed out.
+template <int MODE, bool DEEP>
+static hipError_t launch_near_kernel(const NearArgs& a, hipStream_t s)
+{
+    const size_t lds = (size_t)(a.rules.nt + a.rules.nr) * sizeof(double4);
+    // a fact of the kernel and the GPU (gfx950 alone), asked for once: with the largest rules' LDS
+    static const unsigned long long most = [] {
+        int dev = 0, cus = 0, per_cu = 0;
+        const size_t largest = (size_t)(kMaxTriNodes + kMaxRectNodes) * sizeof(double4);
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, near_kernel<MODE, DEEP>, kBlock, largest) != hipSuccess)
+            (void)hipGetLastError();
+        return (unsigned long long)std::max(1, cus * std::max(1, per_cu));
+    }();
+    const unsigned blocks = (unsigned)std::max<unsigned long long>(1, std::min(most, (a.near_cap + kNearWaves - 1) / kNearWaves));
+    near_kernel<MODE, DEEP><<<blocks, kBlock, lds, s>>>(a);
+    return hipGetLastError();
+}
+
 hipError_t launch_near(const NearArgs& a, int mode, hipStream_t s)
 {
-    // persistent lanes (no more than the list can hold pairs); every lane leaves once the
-    // shared cursor passes the pair count
-    const int blocks = (int)std::max<unsigned long long>(1, std::min<unsigned long long>(1024, (a.near_cap + kBlock - 1) / kBlock));
-    const size_t lds = (size_t)(a.rules.nt + a.rules.nr) * sizeof(double4);
-    if (mode == kNearColloc) near_kernel<kNearColloc, true><<<blocks, kBlock, lds, s>>>(a);
-    else if (mode == kNearGrad) near_kernel<kNearGrad, true><<<blocks, kBlock, lds, s>>>(a);
-    else if (a.deep) near_kernel<kNearEval, true><<<blocks, kBlock, lds, s>>>(a);
-    else near_kernel<kNearEval, false><<<blocks, kBlock, lds, s>>>(a);
-    return hipGetLastError();
+    if (mode == kNearColloc) return launch_near_kernel<kNearColloc, true>(a, s);
+    if (mode == kNearGrad) return launch_near_kernel<kNearGrad, true>(a, s);
+    return a.deep ? launch_near_kernel<kNearEval, true>(a, s) : launch_near_kernel<kNearEval, false>(a, s);
 }
 
 hipError_t launch_near_list(const double* pts, int64_t n, const Elements& el, NearPair* list, unsigned long long cap,
