@@ -449,7 +449,7 @@ int bemc_context::finish(int i)
     const DevCounters& c = *r.h_ctr;
     float far_ms = 0.f, near_ms = 0.f;
     (void)hipEventElapsedTime(&far_ms, r.ev_far0, r.ev_far1);
-    (void)hipEventElapsedTime(&near_ms, r.ev_far1, r.ev_near1);
+    (void)hipEventElapsedTime(&near_ms, r.ev_far1, r.d_ctr ? r.ev_done : r.ev_near1);
     last = bemc_stats{};
     last.pairs = r.pairs;
     last.node_interactions = r.node_ints >= 0 ? r.node_ints : (int64_t)c.node_ints;
@@ -542,15 +542,20 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
     // element split: many more workgroups than resident slots, so that the dispatcher
     // balances the tail; the chunk partial sums are reduced in fixed order
     const int64_t blocks = (npts + 511) / 512;  // nominal 512 points per workgroup (256-768 in fact)
-    int n_split = (int)std::min<int64_t>(kMaxSplit, std::max<int64_t>(1, (kSplitTargetBlocks + blocks - 1) / blocks));
+    int n_split = (int)std::min<int64_t>(colloc ? kMaxSplit : max_split(npts),
+                                         std::max<int64_t>(1, (kSplitTargetBlocks + blocks - 1) / blocks));
     n_split = (int)std::min<int64_t>(n_split, std::max<int64_t>(1, ne / 16));  // chunks of >= 16 elements
+    // few points: an element per lane (launch_far_few), if the chunks' partial sums find room
+    bool few = !colloc && n <= kFewPoints && ne > 0;
+    if (few) n_split = (int)std::min<int64_t>(kFewMaxChunks, (ne + kFewChunk - 1) / kFewChunk);
     const int64_t rows = colloc ? n_rhs_colloc : (grad ? 6 : 4);
-    if (n_split > 1) {
+    if (n_split > 1 || few) {
         const size_t need = (size_t)n_split * (size_t)rows * (size_t)npts;
         if (noalloc) {
-            while (n_split > 1 && (size_t)n_split * (size_t)rows * (size_t)npts > W.partial_cap) --n_split;
+            while (!few && n_split > 1 && (size_t)n_split * (size_t)rows * (size_t)npts > W.partial_cap) --n_split;
         } else if (ensure_partial(need)) {
             n_split = 1;  // not enough memory for the chunks: one chunk
+            few = false;
         }
     }
     // the call record (waits only if the ring is full of calls in flight)
@@ -583,34 +588,41 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
     bool order_cleared = true;
     if (!reuse_near) {
         HIP_TRY(clear_call(W.ctr, W.nw, npts, s));
-        HIP_TRY(launch_near_list(lpts, npts, el, W.near, W.near_cap, W.ctr, s));
+        if (!few) HIP_TRY(launch_near_list(lpts, npts, el, W.near, W.near_cap, W.ctr, s));
     }
-    const bool read_count = near_grow && !noalloc && !reuse_near;
-    if (read_count) {
-        HIP_TRY(hipMemcpyAsync(R.h_list, W.ctr, sizeof(DevCounters), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipEventRecord(R.ev_list, s));
-    }
+    // a list that holds every pair there is cannot overflow: nothing to read
+    const bool read_count = near_grow && !noalloc && !reuse_near &&
+                            (unsigned long long)npts * (unsigned long long)ne > W.near_cap;
+    auto copy_count = [&]() -> hipError_t {
+        const hipError_t e = hipMemcpyAsync(R.h_list, W.ctr, sizeof(DevCounters), hipMemcpyDeviceToHost, s);
+        return e == hipSuccess ? hipEventRecord(R.ev_list, s) : e;
+    };
+    if (read_count && !few) HIP_TRY(copy_count());
 
     FarArgs fa{};
     fa.el = el; fa.rules = rules();
     fa.pts = pts; fa.n = npts; fa.rhs = rhs; fa.n_rhs = n_rhs_colloc; fa.K = coulomb_constant();
     fa.phi = phi; fa.E = E; fa.G = G;
     fa.elem_begin = 0; fa.elem_end = ne; fa.n_split = n_split; fa.chunk = (ne + n_split - 1) / n_split;
-    fa.partial = n_split > 1 ? W.partial : nullptr;
+    fa.partial = n_split > 1 || few ? W.partial : nullptr;
     fa.near_list = W.near; fa.near_cap = W.near_cap; fa.ctr = W.ctr;
     fa.dr_rules = (dr_rules && !colloc) ? 1 : 0;
     fa.lv = levels();
     HIP_TRY(hipEventRecord(R.ev_far0, s));
-    HIP_TRY(colloc ? launch_far_colloc(fa, precision, s)
-                   : (grad ? launch_far_grad(fa, precision, s) : launch_far_eval(fa, precision, s)));
+    HIP_TRY(few ? launch_far_few(fa, mode, s)
+                : (colloc ? launch_far_colloc(fa, precision, s)
+                          : (grad ? launch_far_grad(fa, precision, s) : launch_far_eval(fa, precision, s))));
     HIP_TRY(hipEventRecord(R.ev_far1, s));  // far_ms: the far-field kernel alone
+    if (read_count && few) HIP_TRY(copy_count());
     // (field and gradient: the chunks are added with the near sums at the end)
     if (n_split > 1 && colloc) HIP_TRY(launch_reduce_chunks(W.partial, n_split, rows, npts, fa.K, phi, s));
 
+    bool no_pairs = false;  // known to the host: the near stage is left out
     if (read_count) {
         // the far field runs meanwhile; the list pass finished long before it
         HIP_TRY(hipEventSynchronize(R.ev_list));
         const unsigned long long found = R.h_list->near_count;
+        no_pairs = found == 0;
         if (found > W.near_cap) {  // grow the list and list again
             int rc = ensure_near_capacity(found);
             if (rc) return rc;
@@ -628,8 +640,9 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
     na.near_list = W.near; na.slot = W.nw.slot; na.order = W.nw.order; na.opair = W.nw.opair;
     na.walk_end = near_walk_end(W.nw); na.heavy_end = near_heavy_end(W.nw); na.deep = 1;
     na.res = W.nw.res;
-    if (!reuse_near) {
-        HIP_TRY(near_order(W.near, W.ctr, W.near_cap, npts, lpts, el, W.nw, order_cleared, s));
+    if (!reuse_near && (!no_pairs || colloc)) {
+        if (!colloc && npts <= kOrderSmallPoints) HIP_TRY(near_order_small(W.near, W.ctr, W.near_cap, npts, lpts, el, W.nw, s));
+        else HIP_TRY(near_order(W.near, W.ctr, W.near_cap, npts, lpts, el, W.nw, order_cleared, s));
         HIP_TRY(launch_near(na, mode, s));
     }
     if (colloc) {
@@ -637,14 +650,16 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
     } else {
         // far field (chunk sums) + near sums, back to the caller's order, in one pass
         const int orows = grad ? 6 : (user_E ? 4 : 1);
-        HIP_TRY(near_finish(W.nw, npts, mode, orows, n_split > 1 ? W.partial : nullptr, n_split, (int)rows,
-                            W.ow.res, fa.K, ordered ? W.ow.perm : nullptr, user_phi, grad ? user_phi + n : user_E,
+        HIP_TRY(near_finish(W.nw, npts, mode, orows, fa.partial, n_split, (int)rows,
+                            few ? nullptr : W.ow.res, fa.K, ordered ? W.ow.perm : nullptr, user_phi, grad ? user_phi + n : user_E,
                             W.ctr, R.d_ctr, s));
     }
-    HIP_TRY(hipEventRecord(R.ev_near1, s));
     // the counters: written by that last kernel into the pinned record (one launch fewer per
-    // call), else copied here
-    if (!R.d_ctr) HIP_TRY(hipMemcpyAsync(R.h_ctr, W.ctr, sizeof(DevCounters), hipMemcpyDeviceToHost, s));
+    // call, and the call's end is the near stage's), else copied here
+    if (!R.d_ctr) {
+        HIP_TRY(hipEventRecord(R.ev_near1, s));
+        HIP_TRY(hipMemcpyAsync(R.h_ctr, W.ctr, sizeof(DevCounters), hipMemcpyDeviceToHost, s));
+    }
     HIP_TRY(hipEventRecord(R.ev_done, s));
     if (colloc && own_work) colloc_cached = true;  // later products are ordered after this one
     R.pending = true;

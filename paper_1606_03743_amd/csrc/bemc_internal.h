@@ -151,6 +151,14 @@ hipError_t launch_far_eval(const FarArgs& a, int precision, hipStream_t s);
 hipError_t launch_far_colloc(const FarArgs& a, int precision, hipStream_t s);
 hipError_t launch_far_grad(const FarArgs& a, int precision, hipStream_t s);
 enum NearMode { kNearEval = 0, kNearColloc = 1, kNearGrad = 2 };
+// Few points: an element per lane, near pairs listed by the same launch, always into a.partial
+// (a.n_split chunks of a.chunk elements)
+// (up to here: 150,000 elements, 33-point / 7 x 7, 128 points 0.53 ms, a point per lane 1.1; 256 points 1.06
+// and 0.78; by distance ratio, 128 points 0.41 ms)
+constexpr int64_t kFewPoints = 128;
+constexpr int64_t kFewChunk = 256;     // elements of a chunk (one per lane), more on large geometries
+constexpr int kFewMaxChunks = 1024;
+hipError_t launch_far_few(const FarArgs& a, int mode, hipStream_t s);
 hipError_t launch_near(const NearArgs& a, int mode, hipStream_t s);
 hipError_t launch_charges(const double* sigma, const double* area, double* q, int64_t ne, int n_rhs, hipStream_t s);
 // the near walk's records nrec[ne][kNearRec] from el.cen, el.frame, el.loc and el.thr2 (after an
@@ -175,6 +183,13 @@ hipError_t launch_divide(double* y, const double* x, const double* d, int64_t n,
 // workgroups per resident slot that element splitting aims for (dispatcher load balance)
 constexpr int kSplitTargetBlocks = 16 * 1024;
 constexpr int kMaxSplit = 64;
+// chunks of a launch of n points: 64, and more for fewer than 4,096 points, whose workgroups would
+// not fill the GPU otherwise (the chunk partial sums then stay at those of 4,096 points)
+constexpr int kMaxSplitSmall = 1024;
+constexpr int64_t max_split(int64_t n)
+{
+    return n >= 4096 ? kMaxSplit : (kMaxSplit * 4096 / (n < 1 ? 1 : n) < kMaxSplitSmall ? kMaxSplit * 4096 / (n < 1 ? 1 : n) : kMaxSplitSmall);
+}
 
 double coulomb_constant();
 int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, double tol, int max_iter, int m,
@@ -214,6 +229,10 @@ void near_work_free(NearWork& w);
 // order the list indices by estimated subdivision cost (w.order) for the near kernel;
 // pts [3][n] are the field points of the list (the centroids for collocation); cleared: w's
 // per-point counts and cursors and its buckets are zero already (clear_call), else cleared here
+// At most kOrderSmallPoints points: one workgroup does it all in one launch (w.sorted is not formed)
+constexpr int64_t kOrderSmallPoints = 256;
+hipError_t near_order_small(const NearPair* list, const DevCounters* ctr, unsigned long long cap, int64_t n,
+                            const double* pts, const Elements& el, const NearWork& w, hipStream_t s);
 hipError_t near_order(const NearPair* list, const DevCounters* ctr, unsigned long long cap, int64_t n,
                       const double* pts, const Elements& el, const NearWork& w, bool cleared, hipStream_t s);
 // an evaluation's first launch: zeroes the counters and w's per-point counts and cursors (n

@@ -39,7 +39,9 @@ constexpr int kBlock = 256;       // 4 wavefronts
 constexpr int kTileNodes = 1024;  // Gaussian-point slots of one LDS tile
 constexpr int kMaxTileElems = 64;
 
-__device__ __forceinline__ int tile_elems(int nn) { return nn >= 16 ? kTileNodes / nn : kMaxTileElems; }
+// elements of one LDS tile for nn nodes an element
+template <typename Lds>
+__device__ __forceinline__ int tile_elems(int nn) { return min(Lds::kElems, max(1, Lds::kNodes / nn)); }
 
 __device__ __forceinline__ float rsqrt32(float x) { return __builtin_amdgcn_rsqf(x); }
 
@@ -182,6 +184,19 @@ struct NearBuffer {
         if (n > kListBuf - 64) flush(list, cap, ctr);
     }
 };
+
+// Near pairs straight to the list, one atomic per wavefront that has any (few points: a few
+// wavefronts of a launch do).  Called with every lane of the wavefront active.
+__device__ __forceinline__ void append_near(bool is_near, uint32_t p, uint32_t e, NearPair* list,
+                                            unsigned long long cap, DevCounters* ctr)
+{
+    const unsigned long long m = lane_mask(is_near);
+    if (m == 0ull) return;
+    unsigned long long base = 0;
+    if (lane_id() == 0) base = atomicAdd(&ctr->near_count, (unsigned long long)__popcll(m));
+    base = bcast_u64(base, 0) + lanes_below(m);
+    if (is_near && base < cap) list[base] = NearPair{ p, e };
+}
 
 // ------------------------------------------------------------- near-pair list -----
 // An axis-aligned box: low and high corner.
@@ -383,17 +398,20 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
 // p3 sum w/r^3) is rotated back with the frame.
 enum FrameForm { kFrExp = 0, kFrRows = 1 };
 
-template <bool MIXED, int NRHS>
+// SMALL: half the nodes and elements (24 KB in FP64 instead of 47), for launches of one point per lane,
+// whose registers would allow four workgroups a CU.
+template <bool MIXED, int NRHS, bool SMALL>
 struct TileLds {
+    static constexpr int kNodes = SMALL ? kTileNodes / 2 : kTileNodes, kElems = SMALL ? kMaxTileElems / 2 : kMaxTileElems;
     using T = typename std::conditional<MIXED, float, double>::type;
     using T4 = typename std::conditional<MIXED, float4, double4>::type;
-    T4 nd[kTileNodes];  // (a, b, a^2 + b^2, w), or divided by w^2 as (a, b, a^2 + b^2, 1) / w^2
-    double cx[kMaxTileElems], cy[kMaxTileElems], cz[kMaxTileElems], thr2[kMaxTileElems];
-    T fr[9][kMaxTileElems];      // point rotation: expanded -2 f1, -2 f2 (gradient: f1, f2); rows f1, f2, f3
-    double qr[9][kMaxTileElems]; // rotation back scaled by the charge: expanded -q f1, -q f2;
+    T4 nd[kNodes];  // (a, b, a^2 + b^2, w), or divided by w^2 as (a, b, a^2 + b^2, 1) / w^2
+    double cx[kElems], cy[kElems], cz[kElems], thr2[kElems];
+    T fr[9][kElems];      // point rotation: expanded -2 f1, -2 f2 (gradient: f1, f2); rows f1, f2, f3
+    double qr[9][kElems]; // rotation back scaled by the charge: expanded -q f1, -q f2;
                                  // rows q f1, q f2, q f3
-    double q[NRHS][kMaxTileElems];
-    T lc[6][kMaxTileElems];      // triangles: in-plane coordinates of A, B, C relative to the centroid
+    double q[NRHS][kElems];
+    T lc[6][kElems];      // triangles: in-plane coordinates of A, B, C relative to the centroid
 };
 
 // Orbit structure of the compiled triangle rules (Tables A2-A5 as expanded on the host:
@@ -466,12 +484,12 @@ __device__ __forceinline__ double4 pair_row_slot(const RuleTables& R, int prow, 
 // scale (the constant that the node sums leave out, half_power_scale).
 // GRAD (the gradient's sums): nothing is folded; the first nfold nodes are those of a rule whose
 // orbits are known, the centroid and S21 nodes staged as (0, 0, 0, w) and (s, |n|^2, s^2, w).
-template <bool TRI, bool MIXED, int NRHS, int FR, bool QR, bool GRAD>
-__device__ __forceinline__ void stage_tile(TileLds<MIXED, NRHS>& s, const Elements& el, const RuleTables& R, int nn,
+template <bool TRI, bool MIXED, int FR, bool QR, bool GRAD, typename Lds>
+__device__ __forceinline__ void stage_tile(Lds& s, const Elements& el, const RuleTables& R, int nn,
                                            int64_t t0, int te, int rhs0, int nrhs, int nfold, int prow,
                                            const TriForms& tf, double scale)
 {
-    using T = typename TileLds<MIXED, NRHS>::T;
+    using T = typename Lds::T;
     const int64_t ne = el.ne;
     for (int k = threadIdx.x; k < te; k += kBlock) {
         const int64_t e = t0 + k;
@@ -1076,6 +1094,31 @@ __device__ __forceinline__ void to_frame(const Lds& s, int j, const double (&x)[
     }
 }
 
+// The gradient's tensor in global axes from an element's sums (S5 ... Sg of node_term) and sum w/r^3
+// (s3): out += q (delta_ij s3 - 3 M_ij), see add_element.
+template <typename T>
+__device__ __forceinline__ void add_grad(const T (&f1)[3], const T (&f2)[3], const T (&d)[3], T s3, T S5, T Sa, T Sb,
+                                         T Saa, T Sab, T Sg, double q, double (&out)[6])
+{
+    const T Sbb = Sg - Saa;
+    T v[3], z[3], g1[3], g2[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        v[c] = fma(f1[c], Sa, f2[c] * Sb);
+        z[c] = fma(S5, d[c], -v[c]);
+        g1[c] = fma(f1[c], Saa, f2[c] * Sab);
+        g2[c] = fma(f1[c], Sab, f2[c] * Sbb);
+    }
+    auto M = [&](int u, int w) -> double {
+        return (double)fma(d[u], z[w], fma(-v[u], d[w], fma(f1[u], g1[w], f2[u] * g2[w])));
+    };
+#pragma unroll
+    for (int c = 0; c < 3; ++c) out[c] = fma(q, fma(-3.0, M(c, c), (double)s3), out[c]);
+    out[3] = fma(-3.0 * q, M(0, 1), out[3]);
+    out[4] = fma(-3.0 * q, M(0, 2), out[4]);
+    out[5] = fma(-3.0 * q, M(1, 2), out[5]);
+}
+
 // acc += the element's contribution to point k (charge q, sums o), in FP64.
 //   expanded sums:  phi += q sum w/r;  E += (q S3) d - (q f1) S1 - (q f2) S2;
 //   rows:           phi += q sum w/r;  E += (q f1) E1 + (q f2) E2 + (q f3) p3 S3;
@@ -1115,25 +1158,13 @@ __device__ __forceinline__ void add_element(PointSet<PPT, MODE>& P, int k, doubl
             d[0] *= ri0; d[1] *= ri0; d[2] *= ri0;
             q *= (double)(ri0 * t);
         }
-        const T Sbb = Sg - Saa;
-        T v[3], z[3], g1[3], g2[3], f1[3], f2[3];
+        const T f1[3] = { s.fr[0][j], s.fr[1][j], s.fr[2][j] }, f2[3] = { s.fr[3][j], s.fr[4][j], s.fr[5][j] };
+        double out[6];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            f1[c] = s.fr[c][j];
-            f2[c] = s.fr[3 + c][j];
-            v[c] = fma(f1[c], Sa, f2[c] * Sb);
-            z[c] = fma(S5, d[c], -v[c]);
-            g1[c] = fma(f1[c], Saa, f2[c] * Sab);
-            g2[c] = fma(f1[c], Sab, f2[c] * Sbb);
-        }
-        auto M = [&](int u, int w) -> double {
-            return (double)fma(d[u], z[w], fma(-v[u], d[w], fma(f1[u], g1[w], f2[u] * g2[w])));
-        };
+        for (int c = 0; c < 6; ++c) out[c] = P.acc[c][k];
+        add_grad(f1, f2, d, s3, S5, Sa, Sb, Saa, Sab, Sg, q, out);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) P.acc[c][k] = fma(q, fma(-3.0, M(c, c), (double)s3), P.acc[c][k]);
-        P.acc[3][k] = fma(-3.0 * q, M(0, 1), P.acc[3][k]);
-        P.acc[4][k] = fma(-3.0 * q, M(0, 2), P.acc[4][k]);
-        P.acc[5][k] = fma(-3.0 * q, M(1, 2), P.acc[5][k]);
+        for (int c = 0; c < 6; ++c) P.acc[c][k] = out[c];
     }
 }
 
@@ -1158,12 +1189,12 @@ __device__ __forceinline__ void far_eval_range(const FarArgs& a, Lds& s, PointSe
     constexpr bool FOLD_ = FOLD && FR == kFrExp && !GRAD;
     constexpr bool ORBITS = FOLD_ || (GRAD && TRI && NN > 0);
     const int nn = NN > 0 ? NN : (TRI ? a.rules.nt : a.rules.nr);
-    const int TE = tile_elems(nn);
+    const int TE = tile_elems<Lds>(nn);
     const TriForms tf = fixed_forms<NN, TRI && ORBITS>(nn);
     for (int64_t t0 = e_begin; t0 < e_end; t0 += TE) {
         const int te = (int)min((int64_t)TE, e_end - t0);
         __syncthreads();
-        stage_tile<TRI, MIXED, 1, FR, MODE == kFarField, GRAD>(s, a.el, a.rules, nn, t0, te, a.rhs, 1,
+        stage_tile<TRI, MIXED, FR, MODE == kFarField, GRAD>(s, a.el, a.rules, nn, t0, te, a.rhs, 1,
                                                                ORBITS ? nn : 0, tensor_group<TRI, NN>() > 0 ? 0 : nn,
                                                                tf, sum_scale<MODE, T>());
         __syncthreads();
@@ -1233,7 +1264,7 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
     const double* c = TRI ? a.lv.tri_c : a.lv.rect_c;
     const int o1 = off[1], o2 = off[2], o3 = off[3], nn = off[4];
     const double c0 = c[0], c1 = c[1], c2 = c[2];
-    const int TE = tile_elems(nn);
+    const int TE = tile_elems<Lds>(nn);
     TriForms tf{ 4, { off[0], o1, o2, o3, nn }, { 0, 0, 0, 0 }, { 0, 0, 0, 0 } };
     if (TRI && N0 > 0) {
         tf.nc[0] = TriOrbits<N0>::nc; tf.n21[0] = 3 * TriOrbits<N0>::n21;
@@ -1253,7 +1284,7 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
         // the 7 x 7 last level of the rectangles keeps its weights (rows form)
         const int nfold = N0 == 0 ? 0 : (tensor_group<TRI, N3>() > 0 ? o3 : nn);
         const int prow = tensor_group<TRI, N3>() > 0 ? o3 : nn;
-        stage_tile<TRI, MIXED, 1, FR, !GRAD, GRAD>(s, a.el, a.lv.tab, nn, t0, te, a.rhs, 1, nfold, prow, tf,
+        stage_tile<TRI, MIXED, FR, !GRAD, GRAD>(s, a.el, a.lv.tab, nn, t0, te, a.rhs, 1, nfold, prow, tf,
                                              sum_scale<MODE, T>());
         __syncthreads();
         for (int j = 0; j < te; ++j) {
@@ -1310,6 +1341,24 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
     }
 }
 
+// The wavefronts' term counts (the same in every lane) added up over the workgroup: one atomic per
+// counter and workgroup.
+__device__ __forceinline__ void add_block_terms(unsigned long long terms, unsigned long long terms_pair, DevCounters* ctr)
+{
+    __shared__ unsigned long long sums[2];
+    if (threadIdx.x < 2) sums[threadIdx.x] = 0ull;
+    __syncthreads();
+    if (lane_id() == 0) {
+        atomicAdd(&sums[0], terms);
+        atomicAdd(&sums[1], terms_pair);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && sums[0]) {
+        atomicAdd(&ctr->node_ints, sums[0]);
+        atomicAdd(&ctr->node_ints_pair, sums[1]);
+    }
+}
+
 // DR == false: one rule per kind, NT / NR nodes.  DR == true: levels (T0..T3 / R0..R3).
 // GRAD: field gradient instead of potential and field.  Compiled node counts (NT, NR > 0)
 // are used only for rules whose weights are all positive (their nodes are folded).
@@ -1318,7 +1367,7 @@ __global__ __launch_bounds__(kBlock) void far_eval_kernel(FarArgs a)
 {
     constexpr int MODE = GRAD ? kFarGrad : kFarField;
     constexpr int NO = Sums<MODE>::kOut;
-    __shared__ TileLds<MIXED, 1> s;
+    __shared__ TileLds<MIXED, 1, !MIXED && PPT == 1 && !GRAD> s;
     PointSet<PPT, MODE> P;
     const int64_t base = (int64_t)blockIdx.x * (kBlock * PPT) + threadIdx.x;
 #pragma unroll
@@ -1345,11 +1394,7 @@ __global__ __launch_bounds__(kBlock) void far_eval_kernel(FarArgs a)
             far_eval_dr_range<NT, T1, T2, T3, true, MIXED, PPT, MODE>(a, s, P, e_lo, nt_end, terms, terms_pair);
         if (nr_begin < e_hi)
             far_eval_dr_range<NR, R1, R2, R3, false, MIXED, PPT, MODE>(a, s, P, nr_begin, e_hi, terms, terms_pair);
-        // wavefront totals: one atomic per wavefront
-        if (lane_id() == 0) {
-            if (terms) atomicAdd(&a.ctr->node_ints, terms);
-            if (terms_pair) atomicAdd(&a.ctr->node_ints_pair, terms_pair);
-        }
+        add_block_terms(terms, terms_pair, a.ctr);
     } else {
         if (e_lo < nt_end) far_eval_range<NT, true, MIXED, PPT, MODE, (NT > 0)>(a, s, P, e_lo, nt_end);
         if (nr_begin < e_hi) far_eval_range<NR, false, MIXED, PPT, MODE, (NR > 0)>(a, s, P, nr_begin, e_hi);
@@ -1376,6 +1421,189 @@ __global__ __launch_bounds__(kBlock) void far_eval_kernel(FarArgs a)
     }
 }
 
+// ------------------------------------------------------------ far field: few points -----
+// A handful of points: an element per lane instead of a point per lane.  With one point the lanes
+// of far_eval_kernel's wavefronts would be idle but one, and a workgroup's chunk of elements a
+// serial chain (150,000 elements, rules by distance ratio: far kernel 5,700 us, 14 us so).  Each lane
+// takes its element's record from memory, forms the Gaussian points of the rule (from LDS, the
+// same node for the whole wavefront) in the element's frame and sums them for PF points, all in
+// FP64 whatever the precision asked for: a launch of this size waits for latency, not for
+// arithmetic.  The near pairs go to the list here, so that there is no list pass.  The lanes' sums
+// are added by a fixed butterfly, the wavefronts' in order: chunk partial sums as those of a split
+// launch.
+template <bool DR, int PF, int MODE>
+struct FewRange {
+    static constexpr int NO = Sums<MODE>::kOut, NS = Sums<MODE>::kNode;
+    double x[PF], y[PF], z[PF];
+    bool valid[PF];
+    uint32_t idx[PF];
+    double acc[NO][PF];
+    unsigned long long terms, terms_pair;
+
+    template <bool TRI>
+    __device__ __forceinline__ void run(const FarArgs& a, const double4* __restrict__ nodes, int64_t lo, int64_t hi)
+    {
+        const Elements& el = a.el;
+        const int64_t ne = el.ne;
+        const int* off = TRI ? a.lv.tri_off : a.lv.rect_off;
+        const double* lim = TRI ? a.lv.tri_c : a.lv.rect_c;
+        const int n_nodes = TRI ? a.rules.nt : a.rules.nr;
+        for (int64_t e0 = lo; e0 < hi; e0 += kBlock) {  // (the same trips for every lane)
+            const bool active = e0 + threadIdx.x < hi;
+            const int64_t e = active ? e0 + threadIdx.x : hi - 1;
+            const double c0 = el.cen[e], c1 = el.cen[ne + e], c2 = el.cen[2 * ne + e], thr2 = el.thr2[e];
+            const double f1[3] = { el.frame[e], el.frame[ne + e], el.frame[2 * ne + e] };
+            const double f2[3] = { el.frame[3 * ne + e], el.frame[4 * ne + e], el.frame[5 * ne + e] };
+            double lc[6];
+#pragma unroll
+            for (int c = 0; c < (TRI ? 6 : 3); ++c) lc[c] = el.loc[(int64_t)c * ne + e];
+            const double q = sum_scale<MODE, double>() * el.q[(int64_t)a.rhs * ne + e];
+            double d[PF][3], H[PF], q1[PF], q2[PF], o[NS][PF];
+            bool far[PF];
+            int level = 0;  // of the lane's pairs
+            bool any = false;
+            unsigned long long pair_terms = 0;
+            unsigned n_far = 0;
+#pragma unroll
+            for (int k = 0; k < PF; ++k) {
+                d[k][0] = x[k] - c0; d[k][1] = y[k] - c1; d[k][2] = z[k] - c2;
+                H[k] = fma(d[k][0], d[k][0], fma(d[k][1], d[k][1], d[k][2] * d[k][2]));
+                q1[k] = -2.0 * fma(d[k][0], f1[0], fma(d[k][1], f1[1], d[k][2] * f1[2]));
+                q2[k] = -2.0 * fma(d[k][0], f2[0], fma(d[k][1], f2[1], d[k][2] * f2[2]));
+                const bool near = active && valid[k] && H[k] < thr2;
+                append_near(near, idx[k], (uint32_t)e, a.near_list, a.near_cap, a.ctr);
+                far[k] = active && valid[k] && !near;
+                any |= far[k];
+                if (DR && far[k]) {
+                    const int l = H[k] >= lim[0] * thr2 ? 0 : (H[k] >= lim[1] * thr2 ? 1 : (H[k] >= lim[2] * thr2 ? 2 : 3));
+                    level = max(level, l);
+                    pair_terms += (unsigned)(off[l + 1] - off[l]);
+                    ++n_far;
+                }
+#pragma unroll
+                for (int c = 0; c < NS; ++c) o[c][k] = 0.0;
+            }
+            if (lane_mask(any) == 0ull) continue;
+            int i_lo = 0, i_hi = n_nodes;
+            if (DR) {  // the finest level any pair of the wavefront needs
+                level = lane_mask(level >= 3) ? 3 : (lane_mask(level >= 2) ? 2 : (lane_mask(level >= 1) ? 1 : 0));
+                i_lo = off[level];
+                i_hi = off[level + 1];
+                terms += (unsigned long long)n_far * (unsigned)(i_hi - i_lo);
+                terms_pair += pair_terms;
+            }
+#pragma unroll 2
+            for (int i = i_lo; i < i_hi; ++i) {
+                const double4 R = nodes[i];
+                double na, nb, w;
+                if (TRI) {
+                    na = fma(R.x, lc[0], fma(R.y, lc[2], R.z * lc[4]));
+                    nb = fma(R.x, lc[1], fma(R.y, lc[3], R.z * lc[5]));
+                    w = R.w;
+                } else {
+                    na = fma(R.x, lc[0], R.y * lc[2]);
+                    nb = R.x * lc[1];
+                    w = R.z;
+                }
+                const double g = fma(na, na, nb * nb);
+#pragma unroll
+                for (int k = 0; k < PF; ++k) {
+                    const double r2 = fma(q1[k], na, fma(q2[k], nb, H[k] + g));
+                    if constexpr (MODE == kFarPhi) {
+                        o[0][k] = add_inv_root(w, r2, o[0][k]);
+                    } else if constexpr (MODE == kFarField) {
+                        const double w3 = inv_cube_phi(w, r2, o[0][k]);
+                        o[1][k] = fma(w3, na, o[1][k]);
+                        o[2][k] = fma(w3, nb, o[2][k]);
+                        o[3][k] += w3;
+                    } else {
+                        const double w5 = inv_fifth(w, r2), ua = w5 * na;
+                        o[0][k] += w5;
+                        o[1][k] += ua;
+                        o[2][k] = fma(w5, nb, o[2][k]);
+                        o[3][k] = fma(ua, na, o[3][k]);
+                        o[4][k] = fma(ua, nb, o[4][k]);
+                        o[5][k] = fma(w5, g, o[5][k]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < PF; ++k) {
+                if (!far[k]) continue;
+                if constexpr (MODE == kFarGrad) {
+                    const double s3 = fma(H[k], o[0][k], fma(q1[k], o[1][k], fma(q2[k], o[2][k], o[5][k])));
+                    double out[6];
+#pragma unroll
+                    for (int c = 0; c < 6; ++c) out[c] = acc[c][k];
+                    add_grad(f1, f2, d[k], s3, o[0][k], o[1][k], o[2][k], o[3][k], o[4][k], o[5][k], q, out);
+#pragma unroll
+                    for (int c = 0; c < 6; ++c) acc[c][k] = out[c];
+                } else {
+                    acc[0][k] = fma(q, o[0][k], acc[0][k]);
+                    if constexpr (MODE == kFarField)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c)
+                            acc[1 + c][k] = fma(q, fma(o[3][k], d[k][c], -fma(f1[c], o[1][k], f2[c] * o[2][k])), acc[1 + c][k]);
+                }
+            }
+        }
+    }
+};
+
+template <bool DR, int PF, int MODE>
+__global__ __launch_bounds__(kBlock) void far_few_kernel(FarArgs a)
+{
+    constexpr int NO = Sums<MODE>::kOut;
+    extern __shared__ double4 few_nodes[];  // the rules' nodes (all levels): triangles, rectangles
+    __shared__ double part[kBlock / 64][NO * PF];
+    const RuleTables& R = DR ? a.lv.tab : a.rules;
+    for (int i = threadIdx.x; i < R.nt + R.nr; i += kBlock) {
+        const double* src = i < R.nt ? R.tri + 4 * i : R.rect + 4 * (i - R.nt);
+        few_nodes[i] = make_double4(src[0], src[1], src[2], src[3]);
+    }
+    FewRange<DR, PF, MODE> F;
+    F.terms = F.terms_pair = 0;
+#pragma unroll
+    for (int k = 0; k < PF; ++k) {
+        const int64_t p = (int64_t)blockIdx.y * PF + k;
+        F.valid[k] = p < a.n;
+        F.idx[k] = (uint32_t)p;
+        F.x[k] = F.valid[k] ? a.pts[p] : 0.0;
+        F.y[k] = F.valid[k] ? a.pts[a.n + p] : 0.0;
+        F.z[k] = F.valid[k] ? a.pts[2 * a.n + p] : 0.0;
+#pragma unroll
+        for (int c = 0; c < NO; ++c) F.acc[c][k] = 0.0;
+    }
+    __syncthreads();
+    const int64_t lo = min((int64_t)blockIdx.x * a.chunk, a.el.ne), hi = min(lo + a.chunk, a.el.ne);
+    const int64_t nt = a.el.n_tri;
+    if (lo < nt) F.template run<true>(a, few_nodes, lo, min(hi, nt));
+    if (hi > nt) F.template run<false>(a, few_nodes + R.nt, max(lo, nt), hi);
+    // the lanes' sums by a fixed butterfly, the wavefronts' in order
+    const int wave = threadIdx.x / 64;
+#pragma unroll
+    for (int c = 0; c < NO; ++c)
+#pragma unroll
+        for (int k = 0; k < PF; ++k) {
+            double v = F.acc[c][k];
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+            if (lane_id() == 0) part[wave][c * PF + k] = v;
+        }
+    if (DR) {
+        unsigned long long t = F.terms, tp = F.terms_pair;
+        for (int o = 32; o > 0; o >>= 1) { t += __shfl_xor(t, o); tp += __shfl_xor(tp, o); }
+        add_block_terms(t, tp, a.ctr);
+    }
+    __syncthreads();
+    if (threadIdx.x < NO * PF) {
+        const int c = threadIdx.x / PF, k = threadIdx.x % PF;
+        const int64_t p = (int64_t)blockIdx.y * PF + k;
+        double v = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) v += part[w][threadIdx.x];
+        if (p < a.n) a.partial[((int64_t)blockIdx.x * NO + c) * a.n + p] = v;
+    }
+}
+
 // ------------------------------------------------------- far field: collocation -----
 template <int NN, bool TRI, bool MIXED, int PPT, typename Lds>
 __device__ __forceinline__ void far_colloc_range(const FarArgs& a, Lds& s, const double (&px)[PPT],
@@ -1387,13 +1615,13 @@ __device__ __forceinline__ void far_colloc_range(const FarArgs& a, Lds& s, const
     constexpr int FR = frame_form<TRI, NN, kFarPhi>();
     constexpr bool FOLD = NN > 0 && FR == kFrExp;
     const int nn = NN > 0 ? NN : (TRI ? a.rules.nt : a.rules.nr);
-    const int TE = tile_elems(nn);
+    const int TE = tile_elems<Lds>(nn);
     const int nrhs = a.n_rhs;
     const TriForms tf = fixed_forms<NN, TRI && FOLD>(nn);
     for (int64_t t0 = e_begin; t0 < e_end; t0 += TE) {
         const int te = (int)min((int64_t)TE, e_end - t0);
         __syncthreads();
-        stage_tile<TRI, MIXED, kMaxRhs, FR, false, false>(s, a.el, a.rules, nn, t0, te, 0, nrhs, FOLD ? nn : 0,
+        stage_tile<TRI, MIXED, FR, false, false>(s, a.el, a.rules, nn, t0, te, 0, nrhs, FOLD ? nn : 0,
                                                    tensor_group<TRI, NN>() > 0 ? 0 : nn, tf, sum_scale<kFarPhi, T>());
         __syncthreads();
         for (int j = 0; j < te; ++j) {
@@ -1424,7 +1652,7 @@ __device__ __forceinline__ void far_colloc_range(const FarArgs& a, Lds& s, const
 template <int NT, int NR, bool MIXED, int PPT>
 __global__ __launch_bounds__(kBlock) void far_colloc_kernel(FarArgs a)
 {
-    __shared__ TileLds<MIXED, kMaxRhs> s;
+    __shared__ TileLds<MIXED, kMaxRhs, false> s;
     const int64_t ne = a.el.ne;
     const int64_t base = (int64_t)blockIdx.x * (kBlock * PPT) + threadIdx.x;
     double px[PPT], py[PPT], pz[PPT];
@@ -2318,6 +2546,10 @@ hipError_t far_eval_launch(const FarArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// Points up to which a lane takes one: a workgroup of three per lane would be partly empty (256 points x
+// 150,000 elements, FP64 far kernel 2.13 ms, 0.78 ms with one; by distance ratio 1.42 and 0.76 ms).
+constexpr int64_t kOnePoint = 2048;
+
 // Field points per lane: two for the distance-ratio levels and the run-time rules; for the
 // compiled long rules three in FP64 and one in the mixed path (on the 150k-element cylinder
 // 1 % and 2 % faster than two; four was slower in both).
@@ -2331,14 +2563,15 @@ hipError_t far_eval_dispatch(const FarArgs& a, hipStream_t s)
         const int* r = a.lv.rect_off;
         const bool std_levels = t[1] == 7 && t[2] == 19 && t[3] == 38 && r[1] == 7 && r[2] == 19 && r[3] == 36;
         if (std_levels && t[4] - t[3] == 33 && r[4] - r[3] == 49)
-            return far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, PPT, false>(a, s);
+            return a.n <= kOnePoint ? far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, 1, false>(a, s)
+                                    : far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, PPT, false>(a, s);
         return far_eval_launch<true, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, false>(a, s);
     }
     const int nt = a.rules.nt, nr = a.rules.nr;
     // a small evaluation (fewer than 1024 workgroups at three points per lane: under one
     // wavefront per SIMD and four per CU) takes one point per lane: more wavefronts hide the
     // latency of the dependent FP64 chains
-    const bool small = !MIXED && (a.n + 3 * kBlock - 1) / (3 * kBlock) * a.n_split < 1024;
+    const bool small = !MIXED && (a.n <= kOnePoint || (a.n + 3 * kBlock - 1) / (3 * kBlock) * a.n_split < 1024);
     if (small && nr == 49 && nt == 7) return far_eval_launch<false, 7, 49, 0, 0, 0, 0, 0, 0, MIXED, 1, false>(a, s);
     if (small && nr == 49 && nt == 33) return far_eval_launch<false, 33, 49, 0, 0, 0, 0, 0, 0, MIXED, 1, false>(a, s);
     if (nr == 49) {
@@ -2399,6 +2632,30 @@ hipError_t launch_far_eval(const FarArgs& a, int precision, hipStream_t s)
 {
     if (a.n <= 0) return hipSuccess;
     return precision == 1 ? far_eval_dispatch<true>(a, s) : far_eval_dispatch<false>(a, s);
+}
+
+namespace {
+template <bool DR, int MODE>
+hipError_t far_few_launch(const FarArgs& a, hipStream_t s)
+{
+    const RuleTables& R = DR ? a.lv.tab : a.rules;
+    const size_t lds = (size_t)(R.nt + R.nr) * sizeof(double4);
+    if (a.n <= 2)
+        far_few_kernel<DR, 1, MODE><<<dim3((unsigned)a.n_split, (unsigned)a.n), kBlock, lds, s>>>(a);
+    else
+        far_few_kernel<DR, 4, MODE><<<dim3((unsigned)a.n_split, (unsigned)((a.n + 3) / 4)), kBlock, lds, s>>>(a);
+    return hipGetLastError();
+}
+}  // namespace
+
+// Few points (at most kFewPoints): chunk partial sums, and the near pairs to the list.
+hipError_t launch_far_few(const FarArgs& a, int mode, hipStream_t s)
+{
+    if (a.n <= 0 || a.n > kFewPoints || !a.partial || a.n_split < 1 || a.n_split > 65535 ||
+        a.chunk * a.n_split < a.el.ne)
+        return hipErrorInvalidValue;
+    if (mode == kNearGrad) return a.dr_rules ? far_few_launch<true, kFarGrad>(a, s) : far_few_launch<false, kFarGrad>(a, s);
+    return a.dr_rules ? far_few_launch<true, kFarField>(a, s) : far_few_launch<false, kFarField>(a, s);
 }
 
 hipError_t launch_far_colloc(const FarArgs& a, int precision, hipStream_t s)

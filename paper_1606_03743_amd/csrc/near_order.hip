@@ -26,6 +26,7 @@ namespace bemc {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int64_t kFinishFew = 65536;  // rows x points below which a thread per result does not fill the GPU
 
 __device__ __forceinline__ unsigned long long pair_total(const DevCounters* ctr, unsigned long long cap)
 {
@@ -135,6 +136,45 @@ __global__ void finish_points_kernel(const uint32_t* __restrict__ start, const u
         for (uint32_t m = 0; m < k; ++m) acc += res[(unsigned long long)(s + m) * rec + c];
         v = v + acc;
     }
+    const int64_t q = perm ? (int64_t)perm[p] : p;
+    (c == 0 ? d0 : d1 + (int64_t)(c - 1) * n)[q] = v;
+}
+
+// The same for few points, whose threads would not fill the GPU and whose chunks are many: a
+// wavefront takes one row of P consecutive points, 64 / P lanes to a point, each adding every
+// (64 / P)-th chunk and near record in order; a fixed butterfly adds the lanes.  (777 points, 31,000
+// near records: 39 us with a thread per result, which adds 40 records one after the other; 8 us.)
+template <int P>
+__global__ void finish_few_kernel(const uint32_t* __restrict__ start, const uint32_t* __restrict__ count, int64_t n,
+                                  const double* __restrict__ res, int rec, int rows, int prow,
+                                  const double* __restrict__ partial, int n_split, const double* __restrict__ far,
+                                  double K, const uint32_t* __restrict__ perm, double* __restrict__ d0,
+                                  double* __restrict__ d1, const DevCounters* __restrict__ ctr,
+                                  DevCounters* __restrict__ ctr_out)
+{
+    copy_counters(ctr, ctr_out);
+    constexpr int G = 64 / P;
+    const int64_t per_row = (n + P - 1) / P;
+    const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / 64;
+    if (w >= per_row * rows) return;  // (whole wavefronts)
+    const int c = (int)(w / per_row), lane = threadIdx.x % 64, g = lane / P;
+    const int64_t p = (w - c * per_row) * P + lane % P;
+    double v = 0.0, near = 0.0;
+    if (p < n) {
+        if (n_split > 1 || !far) {
+#pragma unroll 4
+            for (int j = g; j < n_split; j += G) v += partial[((int64_t)j * prow + c) * n + p];
+        }
+        const uint32_t s = start[p], k = count[p];
+#pragma unroll 2
+        for (uint32_t m = g; m < k; m += G) near += res[(unsigned long long)(s + m) * rec + c];
+    }
+    for (int o = P; o < 64; o <<= 1) {
+        v += __shfl_xor(v, o);
+        near += __shfl_xor(near, o);
+    }
+    if (g != 0 || p >= n) return;
+    v = (n_split > 1 || !far ? K * v : far[(int64_t)c * n + p]) + near;
     const int64_t q = perm ? (int64_t)perm[p] : p;
     (c == 0 ? d0 : d1 + (int64_t)(c - 1) * n)[q] = v;
 }
@@ -333,6 +373,77 @@ __global__ void scatter_kernel(const NearPair* __restrict__ list, const DevCount
     }
 }
 
+// The whole ordering of a short list of few points in one launch of one workgroup: cost classes and
+// per-point counts, their starts, both scatters, the ranks (as the kernels above; five launches of
+// a few microseconds each otherwise, on the GPU and in the host's enqueueing).
+constexpr int kSmallBlock = 1024;
+__global__ __launch_bounds__(kSmallBlock) void order_small_kernel(
+    const NearPair* __restrict__ list, const DevCounters* __restrict__ ctr, unsigned long long cap,
+    const double* __restrict__ pts, int64_t n, Elements el, uint8_t* cost, uint32_t* __restrict__ buckets,
+    uint32_t* __restrict__ order, NearPair* __restrict__ opair, uint32_t* __restrict__ start,
+    uint32_t* __restrict__ count, NearPair* grouped, uint32_t* origin, uint32_t* __restrict__ slot)
+{
+    static_assert(kCostClasses == kOrderSmallPoints, "one scan serves both");
+    __shared__ uint32_t hist[2][kCostClasses], first[2][kCostClasses];  // [0] classes, [1] points
+    const int t = threadIdx.x;
+    if (t < 2 * kCostClasses) (&hist[0][0])[t] = 0u;
+    __syncthreads();
+    const uint32_t total = (uint32_t)pair_total(ctr, cap);
+    if (total == 0) {  // (the points' counts are zero already)
+        if (t < kCostClasses) buckets[kCostClasses + t] = 0u;
+        return;
+    }
+    for (uint32_t i = t; i < total; i += kSmallBlock) {
+        const NearPair pr = list[i];
+        const int c = cost_class(pts, n, el, pr);
+        cost[i] = (uint8_t)c;
+        atomicAdd(&hist[0][c], 1u);
+        atomicAdd(&hist[1][pr.point], 1u);
+    }
+    __syncthreads();
+    // class starts: the counts of all higher classes; point starts: of all lower points (inclusive
+    // sums in eight doubling steps, then less the own count)
+    const int which = t / kCostClasses, i0 = t % kCostClasses, i = which == 0 ? kCostClasses - 1 - i0 : i0;
+    if (t < 2 * kCostClasses) first[which][i0] = hist[which][i];
+    for (int o = 1; o < kCostClasses; o <<= 1) {
+        __syncthreads();
+        const uint32_t v = t < 2 * kCostClasses && i0 >= o ? first[which][i0 - o] : 0u;
+        __syncthreads();
+        if (t < 2 * kCostClasses) first[which][i0] += v;
+    }
+    __syncthreads();
+    const uint32_t st = t < 2 * kCostClasses ? first[which][i0] - hist[which][i] : 0u;
+    __syncthreads();
+    if (t < 2 * kCostClasses) {
+        first[which][i] = st;
+        if (which == 0) {
+            buckets[kCostClasses + i] = st;
+        } else if (i < n) {
+            start[i] = st;
+            count[i] = hist[1][i];
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = t; i < total; i += kSmallBlock) {
+        const NearPair pr = list[i];
+        const uint32_t at = atomicAdd(&first[0][cost[i]], 1u);
+        order[at] = i;
+        opair[at] = pr;
+        const uint32_t pos = atomicAdd(&first[1][pr.point], 1u);
+        grouped[pos] = pr;
+        origin[pos] = i;
+    }
+    __threadfence_block();
+    __syncthreads();
+    for (uint32_t i = t; i < total; i += kSmallBlock) {
+        const NearPair v = grouped[i];
+        const uint32_t k = hist[1][v.point], s = first[1][v.point] - k;  // (the cursor stands at the segment's end)
+        uint32_t rank = 0;
+        for (uint32_t j = 0; j < k; ++j) rank += grouped[s + j].elem < v.elem ? 1u : 0u;
+        slot[origin[i]] = s + rank;
+    }
+}
+
 unsigned grid_for(int64_t n)
 {
     const int64_t b = (n + kBlock - 1) / kBlock;
@@ -393,6 +504,15 @@ size_t near_scan_temp_bytes(int64_t n)
     return bytes;
 }
 
+hipError_t near_order_small(const NearPair* list, const DevCounters* ctr, unsigned long long cap, int64_t n,
+                            const double* pts, const Elements& el, const NearWork& w, hipStream_t s)
+{
+    if (n <= 0 || n > kOrderSmallPoints) return hipErrorInvalidValue;
+    order_small_kernel<<<1, kSmallBlock, 0, s>>>(list, ctr, cap, pts, n, el, w.cost, w.buckets, w.order, w.opair,
+                                                 w.start, w.count, w.grouped, w.origin, w.slot);
+    return hipGetLastError();
+}
+
 hipError_t near_order(const NearPair* list, const DevCounters* ctr, unsigned long long cap, int64_t n,
                       const double* pts, const Elements& el, const NearWork& w, bool cleared, hipStream_t s)
 {
@@ -424,10 +544,23 @@ hipError_t near_finish(const NearWork& w, int64_t n, int mode, int rows, const d
 {
     if (n <= 0 || rows <= 0) return hipSuccess;
     if (mode == kNearColloc) return hipErrorInvalidValue;
+    const int rec = mode == kNearGrad ? 6 : 4;
     const int64_t threads = (int64_t)rows * n;
+    if (threads < kFinishFew) {
+        const int P = n <= 32 ? 1 : 8;  // (a row's neighbouring points share the lines of memory read)
+        const int64_t waves = (n + P - 1) / P * rows;
+        const unsigned blocks = (unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
+        if (P == 1)
+            finish_few_kernel<1><<<blocks, kBlock, 0, s>>>(w.start, w.count, n, w.res, rec, rows, prow, partial, n_split,
+                                                           far, K, perm, d0, d1, ctr, ctr_out);
+        else
+            finish_few_kernel<8><<<blocks, kBlock, 0, s>>>(w.start, w.count, n, w.res, rec, rows, prow, partial, n_split,
+                                                           far, K, perm, d0, d1, ctr, ctr_out);
+        return hipGetLastError();
+    }
     if ((threads + kBlock - 1) / kBlock > 0x7fffffff) return hipErrorInvalidValue;
     finish_points_kernel<<<(unsigned)((threads + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-        w.start, w.count, n, w.res, mode == kNearGrad ? 6 : 4, rows, prow, partial, n_split, far, K, perm, d0, d1,
+        w.start, w.count, n, w.res, rec, rows, prow, partial, n_split, far, K, perm, d0, d1,
         ctr, ctr_out);
     return hipGetLastError();
 }
