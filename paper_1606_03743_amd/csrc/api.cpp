@@ -514,7 +514,10 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
     const bool colloc = mode == kNearColloc;
     const bool grad = mode == kNearGrad;
     const int64_t npts = colloc ? ne : n;
-    const int near_rows = colloc ? 1 : (grad ? 6 : 4);
+    // the potential alone has kernels of its own; the allocation-free call keeps the field's, whose
+    // potential is the same bit for bit with and without the field
+    if (mode == kNearEval && !E && !noalloc) mode = kNearPhi;
+    const int near_rows = colloc || mode == kNearPhi ? 1 : (grad ? 6 : 4);
     // errors found in finished earlier calls are reported first, once
     poll_finished();
     if (sticky) {
@@ -548,7 +551,7 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
     // few points: an element per lane (launch_far_few), if the chunks' partial sums find room
     bool few = !colloc && n <= kFewPoints && ne > 0;
     if (few) n_split = (int)std::min<int64_t>(kFewMaxChunks, (ne + kFewChunk - 1) / kFewChunk);
-    const int64_t rows = colloc ? n_rhs_colloc : (grad ? 6 : 4);
+    const int64_t rows = colloc ? n_rhs_colloc : near_rows;
     if (n_split > 1 || few) {
         const size_t need = (size_t)n_split * (size_t)rows * (size_t)npts;
         if (noalloc) {
@@ -601,7 +604,7 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
 
     FarArgs fa{};
     fa.el = el; fa.rules = rules();
-    fa.pts = pts; fa.n = npts; fa.rhs = rhs; fa.n_rhs = n_rhs_colloc; fa.K = coulomb_constant();
+    fa.pts = pts; fa.n = npts; fa.rhs = rhs; fa.n_out = near_rows; fa.n_rhs = n_rhs_colloc; fa.K = coulomb_constant();
     fa.phi = phi; fa.E = E; fa.G = G;
     fa.elem_begin = 0; fa.elem_end = ne; fa.n_split = n_split; fa.chunk = (ne + n_split - 1) / n_split;
     fa.partial = n_split > 1 || few ? W.partial : nullptr;
@@ -649,8 +652,7 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
         HIP_TRY(near_reduce(W.nw, npts, mode, phi, E, G, el.q, ne, n_rhs_colloc, fa.K, W.ctr, R.d_ctr, s));
     } else {
         // far field (chunk sums) + near sums, back to the caller's order, in one pass
-        const int orows = grad ? 6 : (user_E ? 4 : 1);
-        HIP_TRY(near_finish(W.nw, npts, mode, orows, fa.partial, n_split, (int)rows,
+        HIP_TRY(near_finish(W.nw, npts, mode, mode == kNearEval && !user_E ? 1 : near_rows, fa.partial, n_split, (int)rows,
                             few ? nullptr : W.ow.res, fa.K, ordered ? W.ow.perm : nullptr, user_phi, grad ? user_phi + n : user_E,
                             W.ctr, R.d_ctr, s));
     }

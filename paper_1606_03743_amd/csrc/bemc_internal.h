@@ -101,6 +101,7 @@ struct FarArgs {
     const double* pts;       // [3][n] (eval)  -- unused for collocation
     int64_t n;               // field points (eval) or rows (collocation)
     int rhs;                 // density vector (eval)
+    int n_out;               // rows of an evaluation: 4 with the field, 1 potential alone, 6 gradient
     int n_rhs;               // collocation right-hand sides
     double K;                // Coulomb constant
     double* phi;             // [n] (eval) or out[n_rhs][ne] (collocation)
@@ -139,7 +140,7 @@ struct NearArgs {
     int deep;                    // field mode: 1 walks those breadth first, a wavefront each (more
                                  // registers); 0 walks every pair depth first in one lane
     double* res;                 // per-pair result records at the pairs' slots: [slot][4] field,
-                                 // [slot][6] gradient, [slot] collocation
+                                 // [slot][6] gradient, [slot] collocation and potential alone
     DevCounters* ctr;
     double near_dr2;    // near_dr^2
     int max_depth;
@@ -150,7 +151,8 @@ struct NearArgs {
 hipError_t launch_far_eval(const FarArgs& a, int precision, hipStream_t s);
 hipError_t launch_far_colloc(const FarArgs& a, int precision, hipStream_t s);
 hipError_t launch_far_grad(const FarArgs& a, int precision, hipStream_t s);
-enum NearMode { kNearEval = 0, kNearColloc = 1, kNearGrad = 2 };
+// (kNearPhi: potential at field points, no field asked for)
+enum NearMode { kNearEval = 0, kNearColloc = 1, kNearGrad = 2, kNearPhi = 3 };
 // Few points: an element per lane, near pairs listed by the same launch, always into a.partial
 // (a.n_split chunks of a.chunk elements)
 // (up to here: 150,000 elements, 33-point / 7 x 7, 128 points 0.53 ms, a point per lane 1.1; 256 points 1.06

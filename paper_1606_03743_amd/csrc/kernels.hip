@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
 // root of r^2 / w^2 is w/r itself, and (w/r)^3 times the staged values gives the three
 // field sums, which saves the multiplication by the weight per node.
 //
-// Rows form (potential and field of the 7 x 7 Gauss-Legendre rectangle rule): the point is
+// Rows form (the field of the 7 x 7 Gauss-Legendre rectangle rule): the point is
 // rotated into the frame, p = (f1.d, f2.d, f3.d).  For rectangles f1 runs along the second
 // side, so the nodes of a tensor Gauss-Legendre rule that share their first coordinate share
 // b, and are summed in rows (pair_row).  The local field (sum w (p1 - a)/r^3, sum w (p2 - b)/r^3,
@@ -755,10 +755,14 @@ __device__ __forceinline__ void pair_row(const T4* t, int n0, const Local<PPT, T
     T db[PPT], da0[PPT], C[PPT], mq[PPT], sg[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-        db[k] = L.p2[k] - b;
-        da0[k] = L.p1[k] - a0;
         C[k] = fma(L.q1[k], a0, fma(L.q2[k], b, L.H[k] + g0));
-        mq[k] = T(-2) * da0[k];
+        if constexpr (MODE == kFarPhi) {
+            mq[k] = fma(T(2), a0, L.q1[k]);
+        } else {
+            db[k] = L.p2[k] - b;
+            da0[k] = L.p1[k] - a0;
+            mq[k] = T(-2) * da0[k];
+        }
     }
     // the middle node (a = a0)
 #pragma unroll
@@ -1120,6 +1124,7 @@ __device__ __forceinline__ void add_grad(const T (&f1)[3], const T (&f2)[3], con
 }
 
 // acc += the element's contribution to point k (charge q, sums o), in FP64.
+//   potential alone: phi += q sum w/r;
 //   expanded sums:  phi += q sum w/r;  E += (q S3) d - (q f1) S1 - (q f2) S2;
 //   rows:           phi += q sum w/r;  E += (q f1) E1 + (q f2) E2 + (q f3) p3 S3;
 //   gradient:       dE_i/dx_j += q (delta_ij sum w/r^3 - 3 M_ij) with M = sum w (d - n)(d - n)^T / r^5
@@ -1131,7 +1136,9 @@ template <int FR, int PPT, int MODE, typename Lds, typename T>
 __device__ __forceinline__ void add_element(PointSet<PPT, MODE>& P, int k, double q, const Lds& s, int j,
                                             const Local<PPT, T>& L, const T (&o)[Sums<MODE>::kNode][PPT])
 {
-    if constexpr (MODE == kFarField) {
+    if constexpr (MODE == kFarPhi) {
+        P.acc[0][k] = fma(q, (double)o[0][k], P.acc[0][k]);
+    } else if constexpr (MODE == kFarField) {
         P.acc[0][k] = fma(q, (double)o[0][k], P.acc[0][k]);
         if constexpr (FR == kFrExp) {
             const double s1 = (double)o[1][k], s2 = (double)o[2][k], qs3 = q * (double)o[3][k];
@@ -1174,7 +1181,7 @@ constexpr int tensor_group() { return (!TRI && NN == 49) ? 7 : 0; }
 
 // frame form of an element kind with a compiled rule of NN nodes
 template <bool TRI, int NN, int MODE>
-constexpr int frame_form() { return (MODE != kFarGrad && tensor_group<TRI, NN>() > 0) ? kFrRows : kFrExp; }
+constexpr int frame_form() { return (MODE == kFarField && tensor_group<TRI, NN>() > 0) ? kFrRows : kFrExp; }
 
 // One element kind over [e_begin, e_end) with one rule; NN > 0 is the compile-time node
 // count, NN == 0 reads it at run time.  FOLD: the rule's weights are all positive (the
@@ -1186,7 +1193,7 @@ __device__ __forceinline__ void far_eval_range(const FarArgs& a, Lds& s, PointSe
     using T = typename Lds::T;
     constexpr int FR = frame_form<TRI, NN, MODE>();
     constexpr bool GRAD = MODE == kFarGrad;
-    constexpr bool FOLD_ = FOLD && FR == kFrExp && !GRAD;
+    constexpr bool FOLD_ = FOLD && !GRAD && tensor_group<TRI, NN>() == 0;
     constexpr bool ORBITS = FOLD_ || (GRAD && TRI && NN > 0);
     const int nn = NN > 0 ? NN : (TRI ? a.rules.nt : a.rules.nr);
     const int TE = tile_elems<Lds>(nn);
@@ -1258,7 +1265,7 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
 {
     using T = typename Lds::T;
     constexpr bool GRAD = MODE == kFarGrad;
-    constexpr int FR = (TRI || GRAD) ? kFrExp : kFrRows;
+    constexpr int FR = (TRI || MODE != kFarField) ? kFrExp : kFrRows;
     constexpr bool FOLD = N0 > 0 && !GRAD;
     const int* off = TRI ? a.lv.tri_off : a.lv.rect_off;
     const double* c = TRI ? a.lv.tri_c : a.lv.rect_c;
@@ -1284,7 +1291,7 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
         // the 7 x 7 last level of the rectangles keeps its weights (rows form)
         const int nfold = N0 == 0 ? 0 : (tensor_group<TRI, N3>() > 0 ? o3 : nn);
         const int prow = tensor_group<TRI, N3>() > 0 ? o3 : nn;
-        stage_tile<TRI, MIXED, FR, !GRAD, GRAD>(s, a.el, a.lv.tab, nn, t0, te, a.rhs, 1, nfold, prow, tf,
+        stage_tile<TRI, MIXED, FR, MODE == kFarField, GRAD>(s, a.el, a.lv.tab, nn, t0, te, a.rhs, 1, nfold, prow, tf,
                                              sum_scale<MODE, T>());
         __syncthreads();
         for (int j = 0; j < te; ++j) {
@@ -1329,7 +1336,7 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
                 element_sum<N3, G3, FOLD && (TRI || G3 == 0), TRI, PPT, MODE>(s, j, b + o3, nn - o3, L, o);
                 w3 += ec;
             }
-            if constexpr (!TRI && !GRAD) {
+            if constexpr (FR == kFrRows) {
                 // rows form for the rotation back; the 7 x 7 last level is in it already
                 if (!(wl == 3 && tensor_group<TRI, N3>() > 0)) exp_to_rows<PPT>(L, o);
             }
@@ -1360,14 +1367,13 @@ __device__ __forceinline__ void add_block_terms(unsigned long long terms, unsign
 }
 
 // DR == false: one rule per kind, NT / NR nodes.  DR == true: levels (T0..T3 / R0..R3).
-// GRAD: field gradient instead of potential and field.  Compiled node counts (NT, NR > 0)
+// MODE: potential and field, potential alone, or the field gradient.  Compiled node counts (NT, NR > 0)
 // are used only for rules whose weights are all positive (their nodes are folded).
-template <bool DR, int NT, int NR, int T1, int T2, int T3, int R1, int R2, int R3, bool MIXED, int PPT, bool GRAD>
+template <bool DR, int NT, int NR, int T1, int T2, int T3, int R1, int R2, int R3, bool MIXED, int PPT, int MODE>
 __global__ __launch_bounds__(kBlock) void far_eval_kernel(FarArgs a)
 {
-    constexpr int MODE = GRAD ? kFarGrad : kFarField;
     constexpr int NO = Sums<MODE>::kOut;
-    __shared__ TileLds<MIXED, 1, !MIXED && PPT == 1 && !GRAD> s;
+    __shared__ TileLds<MIXED, 1, !MIXED && PPT == 1 && MODE != kFarGrad> s;
     PointSet<PPT, MODE> P;
     const int64_t base = (int64_t)blockIdx.x * (kBlock * PPT) + threadIdx.x;
 #pragma unroll
@@ -1407,15 +1413,15 @@ __global__ __launch_bounds__(kBlock) void far_eval_kernel(FarArgs a)
             double* o = a.partial + (int64_t)blockIdx.y * NO * a.n;
 #pragma unroll
             for (int c = 0; c < NO; ++c) o[c * a.n + p] = P.acc[c][k];
-        } else if (GRAD) {
+        } else if (MODE == kFarGrad) {
 #pragma unroll
             for (int c = 0; c < NO; ++c) a.G[c * a.n + p] = a.K * P.acc[c][k];
         } else {
             a.phi[p] = a.K * P.acc[0][k];
-            if (a.E) {
-                a.E[p] = a.K * P.acc[1][k];
-                a.E[a.n + p] = a.K * P.acc[2][k];
-                a.E[2 * a.n + p] = a.K * P.acc[3][k];
+            if (MODE == kFarField && a.E) {
+                a.E[p] = a.K * P.acc[NO > 1 ? 1 : 0][k];
+                a.E[a.n + p] = a.K * P.acc[NO > 2 ? 2 : 0][k];
+                a.E[2 * a.n + p] = a.K * P.acc[NO > 3 ? 3 : 0][k];
             }
         }
     }
@@ -1613,7 +1619,7 @@ __device__ __forceinline__ void far_colloc_range(const FarArgs& a, Lds& s, const
 {
     using T = typename Lds::T;
     constexpr int FR = frame_form<TRI, NN, kFarPhi>();
-    constexpr bool FOLD = NN > 0 && FR == kFrExp;
+    constexpr bool FOLD = NN > 0 && tensor_group<TRI, NN>() == 0;
     const int nn = NN > 0 ? NN : (TRI ? a.rules.nt : a.rules.nr);
     const int TE = tile_elems<Lds>(nn);
     const int nrhs = a.n_rhs;
@@ -1814,18 +1820,20 @@ __device__ __forceinline__ void node_geometry(const NearState& s, const NearGeom
 //   collocation:  f0 += w/r;
 //   gradient:     f0 += w/r^3, (f1 .. f6) += w (da^2, db^2, dc^2, da db, da dc, db dc)/r^5.
 template <int MODE>
+constexpr bool near_potential() { return MODE == kNearColloc || MODE == kNearPhi; }
+template <int MODE>
 constexpr double near_scale()
 {
-    return MODE == kNearColloc ? HalfPower<1>::kappa
+    return near_potential<MODE>() ? HalfPower<1>::kappa
                                : (MODE == kNearEval ? HalfPower<3>::kappa : HalfPower<5>::kappa);
 }
 template <int MODE>
-constexpr int near_sums() { return MODE == kNearGrad ? 7 : (MODE == kNearColloc ? 1 : 4); }
+constexpr int near_sums() { return MODE == kNearGrad ? 7 : (near_potential<MODE>() ? 1 : 4); }
 template <int MODE>
 __device__ __forceinline__ void near_terms(double w, double da, double db, double dc, double (&f)[7])
 {
     const double r2 = fma(da, da, fma(db, db, dc * dc));
-    if constexpr (MODE == kNearColloc) {
+    if constexpr (near_potential<MODE>()) {
         f[0] = add_inv_root(w, r2, f[0]);
     } else if constexpr (MODE == kNearEval) {
         const double w3 = inv_cube_phi(w, r2, f[0]);
@@ -1908,6 +1916,8 @@ __device__ __forceinline__ void on_element_pairs(const NearArgs& a, unsigned lon
             r[0] = make_double2(nan, nan);
             r[1] = make_double2(nan, nan);
             r[2] = make_double2(nan, nan);
+        } else if (MODE == kNearPhi) {
+            a.res[cur] = a.K * el.q[(int64_t)a.rhs * ne + e] * (s0 * inv_area);
         } else {
             const double Kq = a.K * el.q[(int64_t)a.rhs * ne + e];
             reinterpret_cast<double4*>(a.res)[cur] = make_double4(
@@ -2046,6 +2056,10 @@ __device__ __forceinline__ void write_record(const NearArgs& a, uint32_t e, unsi
         return;
     }
     const double Kq = a.K * el.q[(int64_t)a.rhs * el.ne + e];
+    if (MODE == kNearPhi) {
+        a.res[cur] = Kq * acc[0];
+        return;
+    }
     double F[9];
     {
         const double* rec = el.nrec + (int64_t)e * kNearRec + 3;
@@ -2535,13 +2549,13 @@ __global__ void zero_counters_kernel(DevCounters* c)
     if (i < (int)(sizeof(DevCounters) / sizeof(unsigned long long))) w[i] = 0ull;
 }
 
-template <bool DR, int NT, int NR, int T1, int T2, int T3, int R1, int R2, int R3, bool MIXED, int PPT, bool GRAD>
+template <bool DR, int NT, int NR, int T1, int T2, int T3, int R1, int R2, int R3, bool MIXED, int PPT, int MODE>
 hipError_t far_eval_launch(const FarArgs& a, hipStream_t s)
 {
     const int64_t per = (int64_t)kBlock * PPT;
     const int64_t blocks = (a.n + per - 1) / per;
     if (blocks > 0x7fffffff || a.n_split < 1 || a.n_split > 65535) return hipErrorInvalidValue;
-    far_eval_kernel<DR, NT, NR, T1, T2, T3, R1, R2, R3, MIXED, PPT, GRAD>
+    far_eval_kernel<DR, NT, NR, T1, T2, T3, R1, R2, R3, MIXED, PPT, MODE>
         <<<dim3((unsigned)blocks, (unsigned)a.n_split), dim3(kBlock), 0, s>>>(a);
     return hipGetLastError();
 }
@@ -2563,26 +2577,54 @@ hipError_t far_eval_dispatch(const FarArgs& a, hipStream_t s)
         const int* r = a.lv.rect_off;
         const bool std_levels = t[1] == 7 && t[2] == 19 && t[3] == 38 && r[1] == 7 && r[2] == 19 && r[3] == 36;
         if (std_levels && t[4] - t[3] == 33 && r[4] - r[3] == 49)
-            return a.n <= kOnePoint ? far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, 1, false>(a, s)
-                                    : far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, PPT, false>(a, s);
-        return far_eval_launch<true, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, false>(a, s);
+            return a.n <= kOnePoint ? far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, 1, kFarField>(a, s)
+                                    : far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, PPT, kFarField>(a, s);
+        return far_eval_launch<true, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, kFarField>(a, s);
     }
     const int nt = a.rules.nt, nr = a.rules.nr;
     // a small evaluation (fewer than 1024 workgroups at three points per lane: under one
     // wavefront per SIMD and four per CU) takes one point per lane: more wavefronts hide the
     // latency of the dependent FP64 chains
     const bool small = !MIXED && (a.n <= kOnePoint || (a.n + 3 * kBlock - 1) / (3 * kBlock) * a.n_split < 1024);
-    if (small && nr == 49 && nt == 7) return far_eval_launch<false, 7, 49, 0, 0, 0, 0, 0, 0, MIXED, 1, false>(a, s);
-    if (small && nr == 49 && nt == 33) return far_eval_launch<false, 33, 49, 0, 0, 0, 0, 0, 0, MIXED, 1, false>(a, s);
+    if (small && nr == 49 && nt == 7) return far_eval_launch<false, 7, 49, 0, 0, 0, 0, 0, 0, MIXED, 1, kFarField>(a, s);
+    if (small && nr == 49 && nt == 33) return far_eval_launch<false, 33, 49, 0, 0, 0, 0, 0, 0, MIXED, 1, kFarField>(a, s);
     if (nr == 49) {
-        if (nt == 7) return far_eval_launch<false, 7, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, false>(a, s);
-        if (nt == 12) return far_eval_launch<false, 12, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, false>(a, s);
-        if (nt == 19) return far_eval_launch<false, 19, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, false>(a, s);
-        if (nt == 33) return far_eval_launch<false, 33, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, false>(a, s);
+        if (nt == 7) return far_eval_launch<false, 7, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, kFarField>(a, s);
+        if (nt == 12) return far_eval_launch<false, 12, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, kFarField>(a, s);
+        if (nt == 19) return far_eval_launch<false, 19, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, kFarField>(a, s);
+        if (nt == 33) return far_eval_launch<false, 33, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, kFarField>(a, s);
     }
     if (nr == 33 && nt == 33)  // Table B5 for the rectangles
-        return far_eval_launch<false, 33, 33, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, false>(a, s);
-    return far_eval_launch<false, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, false>(a, s);
+        return far_eval_launch<false, 33, 33, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, kFarField>(a, s);
+    return far_eval_launch<false, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, kFarField>(a, s);
+}
+
+// Potential alone: compiled for the default rules, the 7-point triangle rule and the levels.  FP64: 7
+// instead of 12 FP64 instructions per node beside the reciprocal square root, mixed 5 instead of 9, and
+// no rotation back (131,071 points x 150,000 elements by distance ratio, mixed: far kernel 85.0 -> @@ ms).
+template <bool MIXED>
+hipError_t far_phi_dispatch(const FarArgs& a, hipStream_t s)
+{
+    constexpr int PPT = 2;
+    constexpr int PPT_LONG = MIXED ? 2 : 3;
+    const bool one = a.n <= kOnePoint;
+    if (a.dr_rules) {
+        const int* t = a.lv.tri_off;
+        const int* r = a.lv.rect_off;
+        const bool std_levels = t[1] == 7 && t[2] == 19 && t[3] == 38 && r[1] == 7 && r[2] == 19 && r[3] == 36;
+        if (std_levels && t[4] - t[3] == 33 && r[4] - r[3] == 49)
+            return one ? far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, 1, kFarPhi>(a, s)
+                       : far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, PPT, kFarPhi>(a, s);
+        return far_eval_launch<true, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, kFarPhi>(a, s);
+    }
+    const int nt = a.rules.nt, nr = a.rules.nr;
+    if (nr == 49 && nt == 33)
+        return one ? far_eval_launch<false, 33, 49, 0, 0, 0, 0, 0, 0, MIXED, 1, kFarPhi>(a, s)
+                   : far_eval_launch<false, 33, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, kFarPhi>(a, s);
+    if (nr == 49 && nt == 7)
+        return one ? far_eval_launch<false, 7, 49, 0, 0, 0, 0, 0, 0, MIXED, 1, kFarPhi>(a, s)
+                   : far_eval_launch<false, 7, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, kFarPhi>(a, s);
+    return far_eval_launch<false, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, kFarPhi>(a, s);
 }
 
 // Gradient: compile-time node counts for the default rules only; one point per lane for
@@ -2598,12 +2640,12 @@ hipError_t far_grad_dispatch(const FarArgs& a, hipStream_t s)
         const int* r = a.lv.rect_off;
         const bool std_levels = t[1] == 7 && t[2] == 19 && t[3] == 38 && r[1] == 7 && r[2] == 19 && r[3] == 36;
         if (std_levels && t[4] - t[3] == 33 && r[4] - r[3] == 49)
-            return far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, PPT, true>(a, s);
-        return far_eval_launch<true, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, true>(a, s);
+            return far_eval_launch<true, 7, 7, 12, 19, 33, 12, 17, 49, MIXED, PPT, kFarGrad>(a, s);
+        return far_eval_launch<true, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, kFarGrad>(a, s);
     }
     if (a.rules.nt == 33 && a.rules.nr == 49)
-        return far_eval_launch<false, 33, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, true>(a, s);
-    return far_eval_launch<false, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, true>(a, s);
+        return far_eval_launch<false, 33, 49, 0, 0, 0, 0, 0, 0, MIXED, PPT_LONG, kFarGrad>(a, s);
+    return far_eval_launch<false, 0, 0, 0, 0, 0, 0, 0, 0, MIXED, PPT, kFarGrad>(a, s);
 }
 
 template <int NT, int NR, bool MIXED, int PPT>
@@ -2631,6 +2673,7 @@ hipError_t far_colloc_dispatch(const FarArgs& a, hipStream_t s)
 hipError_t launch_far_eval(const FarArgs& a, int precision, hipStream_t s)
 {
     if (a.n <= 0) return hipSuccess;
+    if (a.n_out == 1) return precision == 1 ? far_phi_dispatch<true>(a, s) : far_phi_dispatch<false>(a, s);
     return precision == 1 ? far_eval_dispatch<true>(a, s) : far_eval_dispatch<false>(a, s);
 }
 
@@ -2655,6 +2698,7 @@ hipError_t launch_far_few(const FarArgs& a, int mode, hipStream_t s)
         a.chunk * a.n_split < a.el.ne)
         return hipErrorInvalidValue;
     if (mode == kNearGrad) return a.dr_rules ? far_few_launch<true, kFarGrad>(a, s) : far_few_launch<false, kFarGrad>(a, s);
+    if (a.n_out == 1) return a.dr_rules ? far_few_launch<true, kFarPhi>(a, s) : far_few_launch<false, kFarPhi>(a, s);
     return a.dr_rules ? far_few_launch<true, kFarField>(a, s) : far_few_launch<false, kFarField>(a, s);
 }
 
@@ -2696,6 +2740,7 @@ hipError_t launch_near(const NearArgs& a, int mode, hipStream_t s)
 {
     if (mode == kNearColloc) return launch_near_kernel<kNearColloc, true>(a, s);
     if (mode == kNearGrad) return launch_near_kernel<kNearGrad, true>(a, s);
+    if (mode == kNearPhi) return launch_near_kernel<kNearPhi, true>(a, s);
     return a.deep ? launch_near_kernel<kNearEval, true>(a, s) : launch_near_kernel<kNearEval, false>(a, s);
 }
 

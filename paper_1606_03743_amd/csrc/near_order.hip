@@ -544,7 +544,7 @@ hipError_t near_finish(const NearWork& w, int64_t n, int mode, int rows, const d
 {
     if (n <= 0 || rows <= 0) return hipSuccess;
     if (mode == kNearColloc) return hipErrorInvalidValue;
-    const int rec = mode == kNearGrad ? 6 : 4;
+    const int rec = mode == kNearGrad ? 6 : (mode == kNearPhi ? 1 : 4);
     const int64_t threads = (int64_t)rows * n;
     if (threads < kFinishFew) {
         const int P = n <= 32 ? 1 : 8;  // (a row's neighbouring points share the lines of memory read)

@@ -406,6 +406,7 @@ bool Server::launch(Slot& s, std::string& err)
     fa.pts = s.d_pts;
     fa.n = n;
     fa.rhs = 0;
+    fa.n_out = 4;
     fa.n_rhs = 1;
     fa.K = K;
     fa.phi = s.d_far;
