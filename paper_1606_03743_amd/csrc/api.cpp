@@ -271,9 +271,11 @@ bool rect_rule_nodes(int spec, std::vector<RectNode>& rn)
 {
     return spec > 0 ? rectangle_gauss_rule(spec, rn) : rectangle_table_rule(-spec, rn);
 }
-// a node table on the device
-int upload_table(const std::vector<double>& t64, double** d64)
+// a node table on the device, followed by 1 / w^2 of its nodes (w: weight's place in a node)
+int upload_table(std::vector<double> t64, int w, double** d64)
 {
+    const size_t n = t64.size() / 4;
+    for (size_t i = 0; i < n; ++i) t64.push_back(1.0 / (t64[4 * i + w] * t64[4 * i + w]));
     dev_free(*d64);
     HIP_TRY(dev_alloc(d64, t64.size()));
     HIP_TRY(hipMemcpy(*d64, t64.data(), t64.size() * 8, hipMemcpyHostToDevice));
@@ -292,9 +294,9 @@ int bemc_context::set_rules_tables()
     std::vector<double> t64, r64;
     pack_tri(tn, t64);
     pack_rect(rn, r64);
-    int rc = upload_table(t64, &d_tri);
+    int rc = upload_table(t64, 3, &d_tri);
     if (rc) return rc;
-    if ((rc = upload_table(r64, &d_rect))) return rc;
+    if ((rc = upload_table(r64, 2, &d_rect))) return rc;
     nt = (int)tn.size();
     nr = (int)rn.size();
     // levels of the distance-ratio rule choice: 7 / 12 / 19 / tri_rule and B2 / B3 / B4 / rect rule
@@ -316,8 +318,8 @@ int bemc_context::set_rules_tables()
         lv_tri_off[l + 1] = lv_tri_off[l] + (int)a.size();
         lv_rect_off[l + 1] = lv_rect_off[l] + (int)b.size();
     }
-    if ((rc = upload_table(lt, &d_lv_tri))) return rc;
-    if ((rc = upload_table(lr, &d_lv_rect))) return rc;
+    if ((rc = upload_table(lt, 3, &d_lv_tri))) return rc;
+    if ((rc = upload_table(lr, 2, &d_lv_rect))) return rc;
     return ok();
 }
 

@@ -35,8 +35,8 @@ constexpr int kMinDrRectNodes = 17;
 // Rule tables in device memory: triangle nodes as (la, lb, lc, w), rectangle nodes as
 // (x, y, w, 0); FP32 copies for the mixed path.
 struct RuleTables {
-    const double* tri;    // [nt][4]  la, lb, lc, w
-    const double* rect;   // [nr][4]  x, y, w, 0  (Gauss-Legendre n x n: node i n + j = (x_i, x_j))
+    const double* tri;    // [nt][4]  la, lb, lc, w, then [nt] 1 / w^2
+    const double* rect;   // [nr][4]  x, y, w, 0  (Gauss-Legendre n x n: node i n + j = (x_i, x_j)), then [nr] 1 / w^2
     int nt, nr;
 };
 

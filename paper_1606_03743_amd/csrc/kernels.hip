@@ -460,13 +460,12 @@ __device__ __forceinline__ double4 pair_row_slot(const RuleTables& R, int prow, 
         const int i = prow + r * 7 + 3;
         const double x = R.rect[4 * i];
         const double b = x * beta, a0 = x * gamma;
-        const double w = R.rect[4 * i + 2];
-        return make_double4(b, a0, FOLDED ? 1.0 / (w * w) : w, fma(a0, a0, b * b));
+        return make_double4(b, a0, FOLDED ? R.rect[4 * R.nr + i] : R.rect[4 * i + 2], fma(a0, a0, b * b));
     }
     const int i = prow + r * 7 + 7 - c;  // j = 6 - (c - 1)
     const double sv = R.rect[4 * i + 1] * alpha, w = R.rect[4 * i + 2];
     if constexpr (FOLDED) {
-        const double iw2 = 1.0 / (w * w);
+        const double iw2 = R.rect[4 * R.nr + i];
         return make_double4(sv * iw2, sv * sv * iw2, iw2, 0.0);
     }
     return make_double4(sv, sv * sv, w, w * sv);
@@ -491,90 +490,91 @@ __device__ __forceinline__ void stage_tile(Lds& s, const Elements& el, const Rul
 {
     using T = typename Lds::T;
     const int64_t ne = el.ne;
-    for (int k = threadIdx.x; k < te; k += kBlock) {
-        const int64_t e = t0 + k;
-        s.cx[k] = el.cen[e];
-        s.cy[k] = el.cen[ne + e];
-        s.cz[k] = el.cen[2 * ne + e];
-        s.thr2[k] = el.thr2[e];
-        for (int r = 0; r < nrhs; ++r) s.q[r][k] = scale * el.q[(int64_t)(rhs0 + r) * ne + e];
-        const double q = QR ? scale * el.q[(int64_t)rhs0 * ne + e] : 0.0;
-        if constexpr (FR == kFrExp) {
-#pragma unroll
-            for (int c = 0; c < 6; ++c) {
-                const double f = el.frame[(int64_t)c * ne + e];
-                s.fr[c][k] = (T)(GRAD ? f : -2.0 * f);
-                if (QR) s.qr[c][k] = -q * f;
-                if (TRI) s.lc[c][k] = (T)el.loc[(int64_t)c * ne + e];
-            }
-        } else {
-#pragma unroll
-            for (int c = 0; c < 9; ++c) {
-                const double f = el.frame[(int64_t)c * ne + e];
-                s.fr[c][k] = (T)f;
-                if (QR) s.qr[c][k] = q * f;
-            }
-        }
+    // as many threads to an element as the workgroup has for a full tile (a power of two): each loads the
+    // element's in-plane coordinates once and forms every per-th node (a thread per node loaded them
+    // for each one and divided to find its element: with the levels' 71 and 85 nodes staging was a
+    // tenth of the kernel; 131,071 points x 150,000 elements, mixed, potential: with the levels'
+    // common case below 53.0 -> 46.9 ms, FP64 field of 100,000 107 -> 100 ms)
+    const int lg = 31 - __builtin_clz((unsigned)(kBlock / tile_elems<Lds>(nn))), per = 1 << lg;
+    const int j = threadIdx.x >> lg, sub = threadIdx.x & (per - 1);
+    if (j >= te) return;
+    const int64_t e = t0 + j;
+    const double q = QR ? scale * el.q[(int64_t)rhs0 * ne + e] : 0.0;
+    if (sub == 0) {
+        s.cx[j] = el.cen[e];
+        s.cy[j] = el.cen[ne + e];
+        s.cz[j] = el.cen[2 * ne + e];
+        s.thr2[j] = el.thr2[e];
     }
-    for (int k = threadIdx.x; k < te * nn; k += kBlock) {
-        const int j = k / nn;
-        const int i = k - j * nn;
-        const int64_t e = t0 + j;
+    for (int r = sub; r < nrhs; r += per) s.q[r][j] = scale * el.q[(int64_t)(rhs0 + r) * ne + e];
+    for (int c = sub; c < (FR == kFrExp ? 6 : 9); c += per) {
+        const double f = el.frame[(int64_t)c * ne + e];
+        s.fr[c][j] = (T)(FR == kFrExp && !GRAD ? -2.0 * f : f);
+        if (QR) s.qr[c][j] = FR == kFrExp ? -q * f : q * f;
+    }
+    double lo[6];  // triangle: vertices in the frame; rectangle: gamma, beta, alpha
+#pragma unroll
+    for (int c = 0; c < (TRI ? 6 : 3); ++c) lo[c] = el.loc[(int64_t)c * ne + e];
+    if (TRI && sub == per - 1) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) s.lc[c][j] = (T)lo[c];
+    }
+    auto put = [&](int i, double x, double y, double z, double w) {
+        if constexpr (MIXED) s.nd[j * nn + i] = make_float4((float)x, (float)y, (float)z, (float)w);
+        else s.nd[j * nn + i] = make_double4(x, y, z, w);
+    };
+    for (int i = sub; i < nn; i += per) {
         if (!TRI && i >= prow) {
             if (i - prow < kPairRowSlots) {
-                const double4 v = pair_row_slot<!MIXED && !GRAD>(R, prow, i - prow, el.loc[e], el.loc[ne + e], el.loc[2 * ne + e]);
-                if constexpr (MIXED) s.nd[k] = make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
-                else s.nd[k] = v;
+                const double4 v = pair_row_slot<!MIXED && !GRAD>(R, prow, i - prow, lo[0], lo[1], lo[2]);
+                put(i, v.x, v.y, v.z, v.w);
             }
             continue;
         }
+        const double* node = (TRI ? R.tri : R.rect) + 4 * i;
+        const double iw2 = GRAD ? 1.0 : (TRI ? R.tri[4 * R.nt + i] : R.rect[4 * R.nr + i]);
         double a, b, w;
         if (TRI) {
-            const double la = R.tri[4 * i], lb = R.tri[4 * i + 1], lc = R.tri[4 * i + 2];
-            w = R.tri[4 * i + 3];
+            const double la = node[0], lb = node[1], lc = node[2];
+            w = node[3];
             if (i < nfold) {
                 // the level of node i (selects, not indexing: the forms stay in registers)
                 int off_l = tf.off[0], nc_l = tf.nc[0], n21_l = tf.n21[0];
 #pragma unroll
-                for (int q = 1; q < 4; ++q)
-                    if (q < tf.nlev && i >= tf.off[q]) { off_l = tf.off[q]; nc_l = tf.nc[q]; n21_l = tf.n21[q]; }
+                for (int l = 1; l < 4; ++l)
+                    if (l < tf.nlev && i >= tf.off[l]) { off_l = tf.off[l]; nc_l = tf.nc[l]; n21_l = tf.n21[l]; }
                 const int il = i - off_l;
                 if (il < nc_l + n21_l) {
-                    const double iw2 = GRAD ? 1.0 : 1.0 / (w * w);
                     double v0 = 0.0, v1 = 0.0;
                     if (il >= nc_l) {  // S21: the distinct coordinate at vertex kk
                         const int kk = (il - nc_l) % 3;
                         const double lk = kk == 0 ? la : (kk == 1 ? lb : lc);
                         const double lk1 = kk == 0 ? lb : (kk == 1 ? lc : la);
                         const double sv = lk - lk1;
-                        const double na = sv * el.loc[(int64_t)(2 * kk) * ne + e], nb = sv * el.loc[(int64_t)(2 * kk + 1) * ne + e];
+                        const double na = sv * (kk == 0 ? lo[0] : (kk == 1 ? lo[2] : lo[4]));
+                        const double nb = sv * (kk == 0 ? lo[1] : (kk == 1 ? lo[3] : lo[5]));
                         v0 = sv * iw2;
                         v1 = fma(na, na, nb * nb) * iw2;
                     }
-                    const double v2 = GRAD ? v0 * v0 : iw2, v3 = GRAD ? w : 0.0;
-                    if constexpr (MIXED) s.nd[k] = make_float4((float)v0, (float)v1, (float)v2, (float)v3);
-                    else s.nd[k] = make_double4(v0, v1, v2, v3);
+                    put(i, v0, v1, GRAD ? v0 * v0 : iw2, GRAD ? w : 0.0);
                     continue;
                 }
             }
-            a = la * el.loc[e] + lb * el.loc[2 * ne + e] + lc * el.loc[4 * ne + e];
-            b = la * el.loc[ne + e] + lb * el.loc[3 * ne + e] + lc * el.loc[5 * ne + e];
+            a = la * lo[0] + lb * lo[2] + lc * lo[4];
+            b = la * lo[1] + lb * lo[3] + lc * lo[5];
         } else {
-            const double x = R.rect[4 * i], y = R.rect[4 * i + 1];
-            w = R.rect[4 * i + 2];
-            a = x * el.loc[e] + y * el.loc[2 * ne + e];
-            b = x * el.loc[ne + e];
+            w = node[2];
+            a = node[0] * lo[0] + node[1] * lo[2];
+            b = node[0] * lo[1];
         }
         double g = fma(a, a, b * b);
         if (!GRAD && i < nfold) {
-            const double iw2 = 1.0 / (w * w);
             a *= iw2;
             b *= iw2;
             g *= iw2;
             w = iw2;
         }
-        if constexpr (MIXED) s.nd[k] = make_float4((float)a, (float)b, (float)g, (float)w);
-        else s.nd[k] = make_double4(a, b, g, w);
+        put(i, a, b, g, w);
     }
 }
 
@@ -1269,10 +1269,13 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
     constexpr bool FOLD = N0 > 0 && !GRAD;
     const int* off = TRI ? a.lv.tri_off : a.lv.rect_off;
     const double* c = TRI ? a.lv.tri_c : a.lv.rect_c;
-    const int o1 = off[1], o2 = off[2], o3 = off[3], nn = off[4];
+    constexpr bool FIXED = N0 > 0;  // the levels' sizes are known
+    const int o1 = FIXED ? N0 : off[1], o2 = FIXED ? N0 + N1 : off[2], o3 = FIXED ? N0 + N1 + N2 : off[3];
+    const int nn = FIXED ? N0 + N1 + N2 + N3 : off[4];
     const double c0 = c[0], c1 = c[1], c2 = c[2];
+    const double c_all = fmax(c0, 1.0);  // (a level's limit may lie below the near one's: no near pair passes)
     const int TE = tile_elems<Lds>(nn);
-    TriForms tf{ 4, { off[0], o1, o2, o3, nn }, { 0, 0, 0, 0 }, { 0, 0, 0, 0 } };
+    TriForms tf{ 4, { 0, o1, o2, o3, nn }, { 0, 0, 0, 0 }, { 0, 0, 0, 0 } };
     if (TRI && N0 > 0) {
         tf.nc[0] = TriOrbits<N0>::nc; tf.n21[0] = 3 * TriOrbits<N0>::n21;
         tf.nc[1] = TriOrbits<N1>::nc; tf.n21[1] = 3 * TriOrbits<N1>::n21;
@@ -1282,6 +1285,9 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
     unsigned long long vmask[PPT];  // the lanes with a point, per point of the lane
 #pragma unroll
     for (int k = 0; k < PPT; ++k) vmask[k] = lane_mask(P.valid[k]);
+    unsigned n_valid = 0;
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) n_valid += (unsigned)__popcll(vmask[k]);
     for (int64_t t0 = e_begin; t0 < e_end; t0 += TE) {
         const int te = (int)min((int64_t)TE, e_end - t0);
         // the tile's pair counts (scalar, 32 bits: at most 64 PPT TE per tile): summed by the
@@ -1303,6 +1309,23 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
             // comparisons: pairs for which level 0 suffices, then level 1, level 2, and every far
             // pair (near pairs are listed by near_list_kernel and contribute nothing here); the
             // wavefront's level and the term counts are then scalar work on the masks
+            {
+                // the common case first: level 0 for every pair and none near: one comparison a pair
+                // instead of four, and nothing masked
+                const double all0 = c_all * thr2;
+                unsigned long long short_of = 0;
+#pragma unroll
+                for (int k = 0; k < PPT; ++k) short_of |= vmask[k] & ~lane_mask(D2[k] >= all0);
+                if (short_of == 0) {
+                    T o[Sums<MODE>::kNode][PPT];
+                    element_sum<N0, 0, FOLD, TRI, PPT, MODE>(s, j, j * nn, o1, L, o);
+                    if constexpr (FR == kFrRows) exp_to_rows<PPT>(L, o);
+#pragma unroll
+                    for (int k = 0; k < PPT; ++k) add_element<FR, PPT, MODE>(P, k, q, s, j, L, o);
+                    nc += n_valid; n0 += n_valid; w0 += n_valid;
+                    continue;
+                }
+            }
             const double lim0 = c0 * thr2, lim1 = c1 * thr2, lim2 = c2 * thr2;
             bool far[PPT];
             unsigned long long u0 = 0, u1 = 0, u2 = 0, u3 = 0;  // the lanes with a pair at each level
@@ -2601,7 +2624,7 @@ hipError_t far_eval_dispatch(const FarArgs& a, hipStream_t s)
 
 // Potential alone: compiled for the default rules, the 7-point triangle rule and the levels.  FP64: 7
 // instead of 12 FP64 instructions per node beside the reciprocal square root, mixed 5 instead of 9, and
-// no rotation back (131,071 points x 150,000 elements by distance ratio, mixed: far kernel 85.0 -> @@ ms).
+// no rotation back (131,071 points x 150,000 elements by distance ratio, mixed: far kernel 85.0 -> 52.6 ms).
 template <bool MIXED>
 hipError_t far_phi_dispatch(const FarArgs& a, hipStream_t s)
 {
