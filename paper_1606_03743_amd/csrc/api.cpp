@@ -547,7 +547,7 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
     // element split: many more workgroups than resident slots, so that the dispatcher
     // balances the tail; the chunk partial sums are reduced in fixed order
     const int64_t blocks = (npts + 511) / 512;  // nominal 512 points per workgroup (256-768 in fact)
-    int n_split = (int)std::min<int64_t>(colloc ? kMaxSplit : max_split(npts),
+    int n_split = (int)std::min<int64_t>(max_split(npts),
                                          std::max<int64_t>(1, (kSplitTargetBlocks + blocks - 1) / blocks));
     n_split = (int)std::min<int64_t>(n_split, std::max<int64_t>(1, ne / 16));  // chunks of >= 16 elements
     // few points: an element per lane (launch_far_few), if the chunks' partial sums find room
@@ -619,8 +619,7 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
                           : (grad ? launch_far_grad(fa, precision, s) : launch_far_eval(fa, precision, s))));
     HIP_TRY(hipEventRecord(R.ev_far1, s));  // far_ms: the far-field kernel alone
     if (read_count && few) HIP_TRY(copy_count());
-    // (field and gradient: the chunks are added with the near sums at the end)
-    if (n_split > 1 && colloc) HIP_TRY(launch_reduce_chunks(W.partial, n_split, rows, npts, fa.K, phi, s));
+    // (the chunks are added with the near sums at the end)
 
     bool no_pairs = false;  // known to the host: the near stage is left out
     if (read_count) {
@@ -651,7 +650,7 @@ int bemc_context::run(int mode, const double* pts, int64_t n, int precision, int
         HIP_TRY(launch_near(na, mode, s));
     }
     if (colloc) {
-        HIP_TRY(near_reduce(W.nw, npts, mode, phi, E, G, el.q, ne, n_rhs_colloc, fa.K, W.ctr, R.d_ctr, s));
+        HIP_TRY(near_reduce(W.nw, W.partial, n_split, phi, el.q, ne, n_rhs_colloc, fa.K, W.ctr, R.d_ctr, s));
     } else {
         // far field (chunk sums) + near sums, back to the caller's order, in one pass
         HIP_TRY(near_finish(W.nw, npts, mode, mode == kNearEval && !user_E ? 1 : near_rows, fa.partial, n_split, (int)rows,

@@ -166,8 +166,6 @@ hipError_t launch_charges(const double* sigma, const double* area, double* q, in
 // the near walk's records nrec[ne][kNearRec] from el.cen, el.frame, el.loc and el.thr2 (after an
 // upload, and after the thresholds change)
 hipError_t launch_pack_near_records(const Elements& el, double* nrec, hipStream_t s);
-hipError_t launch_reduce_chunks(const double* partial, int n_split, int64_t rows, int64_t n, double K, double* out,
-                                hipStream_t s);
 hipError_t launch_zero_counters(DevCounters* c, hipStream_t s);
 hipError_t launch_reset_near_count(DevCounters* c, hipStream_t s);  // near_count = 0 only
 // the list pass's and the near stage's counters = 0 (before the near stage runs again)
@@ -178,6 +176,9 @@ hipError_t launch_near_list(const double* pts, int64_t n, const Elements& el, Ne
 
 hipError_t launch_self_diag(const Elements& el, double K, double* diag, hipStream_t s);
 hipError_t launch_multi_dot(const double* V, int k, int64_t n, const double* w, double* partial, int blocks, hipStream_t s);
+constexpr int kMaxCombine = 256;  // vectors of one combination (restart lengths go to 200)
+struct CombineCoef { double c[kMaxCombine]; };
+// c: k <= kMaxCombine coefficients in host memory, copied into the launch
 hipError_t launch_combine(double* y, double a, const double* V, const double* c, int k, int64_t n, const double* d,
                           hipStream_t s);
 hipError_t launch_divide(double* y, const double* x, const double* d, int64_t n, hipStream_t s);
@@ -253,11 +254,10 @@ hipError_t near_finish(const NearWork& w, int64_t n, int mode, int rows, const d
 inline const uint32_t* near_walk_end(const NearWork& w) { return w.buckets + kCostClasses + kOnElementClass; }
 // entries of w.order with deep subdivisions (all classes from kDeepClass up come first)
 inline const uint32_t* near_heavy_end(const NearWork& w) { return w.buckets + kCostClasses + (kDeepClass - 1); }
-// add each point's segment of per-pair result records to its outputs (collocation; field and
-// gradient evaluations use near_finish)
-hipError_t near_reduce(const NearWork& w, int64_t n, int mode, double* phi, double* E,
-                       double* G, const double* q, int64_t ne, int n_rhs, double K, const DevCounters* ctr,
-                       DevCounters* ctr_out, hipStream_t s);
+// the final values of a collocation product: K times the chunk partial sums partial[n_split][n_rhs][ne] (n_split
+// > 1; else phi[n_rhs][ne] holds the far field) plus each centroid's near records times the charges q
+hipError_t near_reduce(const NearWork& w, const double* partial, int n_split, double* phi, const double* q, int64_t ne,
+                       int n_rhs, double K, const DevCounters* ctr, DevCounters* ctr_out, hipStream_t s);
 constexpr unsigned long long kMaxNearPairs = 0xffffffffull;  // 32-bit segment offsets
 
 // Allocation-free evaluation (noalloc.hip): a static device array per GPU, carved into the

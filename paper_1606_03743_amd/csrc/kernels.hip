@@ -2554,17 +2554,6 @@ __global__ void charges_kernel(const double* sigma, const double* area, double* 
     q[i] = sigma[i] * area[i % ne];
 }
 
-// out[m][p] = K * sum over the element chunks k (fixed order) of partial[k][m][p]
-__global__ void reduce_chunks_kernel(const double* partial, int n_split, int64_t rows, int64_t n, double K,
-                                     double* out)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= rows * n) return;
-    double s = 0.0;
-    for (int k = 0; k < n_split; ++k) s += partial[(int64_t)k * rows * n + i];
-    out[i] = K * s;
-}
-
 __global__ void zero_counters_kernel(DevCounters* c)
 {
     unsigned long long* w = reinterpret_cast<unsigned long long*>(c);
@@ -2687,7 +2676,12 @@ template <bool MIXED>
 hipError_t far_colloc_dispatch(const FarArgs& a, hipStream_t s)
 {
     constexpr int PPT = MIXED ? 2 : 3;
-    if (a.rules.nr == 49 && a.rules.nt == 33) return far_colloc_launch<33, 49, MIXED, PPT>(a, s);
+    if (a.rules.nr == 49 && a.rules.nt == 33) {
+        // few workgroups at PPT points per lane: one point (FP64, 2,976 elements 208 -> 165 us, 8,000 elements
+        // 1.05 -> 0.91 ms; mixed 111 -> 96 us and 0.42 -> 0.47 ms, where the node reads bound it)
+        if ((a.el.ne + PPT * kBlock - 1) / (PPT * kBlock) * a.n_split < (MIXED ? 768 : 2048)) return far_colloc_launch<33, 49, MIXED, 1>(a, s);
+        return far_colloc_launch<33, 49, MIXED, PPT>(a, s);
+    }
     return far_colloc_launch<0, 0, MIXED, PPT>(a, s);
 }
 
@@ -2798,15 +2792,6 @@ hipError_t launch_charges(const double* sigma, const double* area, double* q, in
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_chunks(const double* partial, int n_split, int64_t rows, int64_t n, double K, double* out,
-                                hipStream_t s)
-{
-    const int64_t tot = rows * n;
-    if (tot <= 0) return hipSuccess;
-    reduce_chunks_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(partial, n_split, rows, n, K, out);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------------ solver support -------
 // Potential of an element with unit density at its own centroid, K times the exact polar
 // integral (per edge at distance h with end offsets t1, t2: h [asinh(t2/h) - asinh(t1/h)]):
@@ -2849,36 +2834,34 @@ __global__ void self_diag_kernel(Elements el, double K, double* __restrict__ dia
     diag[e] = K * sum;
 }
 
-// partial[j][b] = sum over block b's share of V[j][i] * w[i], j < k (fixed order)
-__global__ void multi_dot_kernel(const double* __restrict__ V, int k, int64_t n, const double* __restrict__ w,
+// partial[j][b] = sum over block b's share of V[j][i] * w[i] (fixed order); blockIdx.y = j < k: the vectors
+// side by side (one after the other in a workgroup, each waited for the last one's reduction)
+__global__ void multi_dot_kernel(const double* __restrict__ V, int64_t n, const double* __restrict__ w,
                                  double* __restrict__ partial)
 {
-    __shared__ double red[256];
-    for (int j = 0; j < k; ++j) {
-        double acc = 0.0;
-        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-            acc = fma(V[(int64_t)j * n + i], w[i], acc);
-        red[threadIdx.x] = acc;
-        __syncthreads();
-        for (int o = 128; o > 0; o >>= 1) {
-            if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) partial[(int64_t)j * gridDim.x + blockIdx.x] = red[0];
-        __syncthreads();
-    }
+    __shared__ double red[4];
+    const int j = blockIdx.y;
+    double acc = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        acc = fma(V[(int64_t)j * n + i], w[i], acc);
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    if (lane_id() == 0) red[threadIdx.x / 64] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) partial[(int64_t)j * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // y[i] = a * y[i] + sum_j c[j] V[j][i] / d[i]^p  (p = 0 or 1; d may be null when p = 0)
-__global__ void combine_kernel(double* __restrict__ y, double a, const double* __restrict__ V, const double* __restrict__ c,
-                               int k, int64_t n, const double* __restrict__ d)
+// The coefficients come with the launch: no copy to wait for.
+__global__ void combine_kernel(double* __restrict__ y, double a, const double* __restrict__ V, CombineCoef c, int k,
+                               int64_t n, const double* __restrict__ d)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     double s = 0.0;
-    for (int j = 0; j < k; ++j) s = fma(c[j], V[(int64_t)j * n + i], s);
+#pragma unroll 4
+    for (int j = 0; j < k; ++j) s = fma(c.c[j], V[(int64_t)j * n + i], s);
     if (d) s /= d[i];
-    y[i] = fma(a, y[i], s);
+    y[i] = a == 0.0 ? s : fma(a, y[i], s);  // (a = 0: y need not hold numbers yet)
 }
 
 // y[i] = x[i] / d[i]
@@ -2930,7 +2913,8 @@ hipError_t launch_self_diag(const Elements& el, double K, double* diag, hipStrea
 
 hipError_t launch_multi_dot(const double* V, int k, int64_t n, const double* w, double* partial, int blocks, hipStream_t s)
 {
-    multi_dot_kernel<<<blocks, 256, 0, s>>>(V, k, n, w, partial);
+    if (k < 1) return hipSuccess;
+    multi_dot_kernel<<<dim3((unsigned)blocks, (unsigned)k), 256, 0, s>>>(V, n, w, partial);
     return hipGetLastError();
 }
 
@@ -2938,7 +2922,10 @@ hipError_t launch_combine(double* y, double a, const double* V, const double* c,
                           hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    combine_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(y, a, V, c, k, n, d);
+    if (k < 0 || k > kMaxCombine) return hipErrorInvalidValue;
+    CombineCoef coef;
+    for (int j = 0; j < k; ++j) coef.c[j] = c[j];
+    combine_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(y, a, V, coef, k, n, d);
     return hipGetLastError();
 }
 

@@ -16,14 +16,19 @@
 
 namespace bemc {
 
+namespace {
+// workgroups of a dot product: each at least 2,048 elements (the host adds their sums)
+int dot_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(256, n / 2048)); }
+}  // namespace
+
 int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, double tol, int max_iter, int m,
                 int precision, bemc_solve_info* info, hipStream_t s, std::string& err)
 {
     using clock = std::chrono::steady_clock;
     const auto t_start = clock::now();
     const int64_t n = el.ne;
-    const int kDotBlocks = 256;
-    double *V = nullptr, *w = nullptr, *t = nullptr, *diag = nullptr, *partial = nullptr, *coef = nullptr;
+    const int kDotBlocks = dot_blocks(n);
+    double *V = nullptr, *w = nullptr, *t = nullptr, *diag = nullptr, *partial = nullptr;
     double* h_partial = nullptr;
     int rc = BEMC_OK;
     auto check = [&](hipError_t e, const char* what) {
@@ -38,7 +43,6 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
         hipMalloc(reinterpret_cast<void**>(&t), sizeof(double) * n) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&diag), sizeof(double) * n) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&partial), sizeof(double) * (size_t)(m + 1) * kDotBlocks) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&coef), sizeof(double) * (m + 1)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&h_partial), sizeof(double) * (size_t)(m + 1) * kDotBlocks,
                       hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -58,10 +62,6 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
             out[j] = acc;
         }
         return true;
-    };
-    auto put_coef = [&](const double* c, int k) {
-        return check(hipMemcpyAsync(coef, c, sizeof(double) * k, hipMemcpyHostToDevice, s), "copy") &&
-               check(hipStreamSynchronize(s), "sync");
     };
     // y = A v (potential at all centroids from densities v)
     int products = 0;
@@ -87,7 +87,7 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
         double beta = bnorm;  // V[0] holds the unnormalised residual
         while (!converged && rc == BEMC_OK && products < max_iter) {
             const double inv = 1.0 / beta;
-            if (!put_coef(&inv, 1) || !check(launch_combine(V, 0.0, V, coef, 1, n, nullptr, s), "scale")) break;
+            if (!check(launch_combine(V, 0.0, V, &inv, 1, n, nullptr, s), "scale")) break;
             std::fill(g.begin(), g.end(), 0.0);
             g[0] = beta;
             int j = 0;
@@ -97,12 +97,10 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
                 // two passes of classical Gram-Schmidt against v_0 .. v_j
                 if (!dots(V, j + 1, w, hcol.data())) break;
                 for (int i = 0; i <= j; ++i) hcol[i] = -hcol[i];
-                if (!put_coef(hcol.data(), j + 1) || !check(launch_combine(w, 1.0, V, coef, j + 1, n, nullptr, s), "axpy"))
-                    break;
+                if (!check(launch_combine(w, 1.0, V, hcol.data(), j + 1, n, nullptr, s), "axpy")) break;
                 if (!dots(V, j + 1, w, h2.data())) break;
                 for (int i = 0; i <= j; ++i) h2[i] = -h2[i];
-                if (!put_coef(h2.data(), j + 1) || !check(launch_combine(w, 1.0, V, coef, j + 1, n, nullptr, s), "axpy"))
-                    break;
+                if (!check(launch_combine(w, 1.0, V, h2.data(), j + 1, n, nullptr, s), "axpy")) break;
                 double hn = 0.0;
                 if (!dots(w, 1, w, &hn)) break;
                 hn = std::sqrt(hn);
@@ -110,12 +108,7 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
                 H[(size_t)(j + 1) * m + j] = hn;
                 if (hn > 0.0) {
                     const double invh = 1.0 / hn;
-                    if (!check(hipMemcpyAsync(V + (size_t)(j + 1) * n, w, sizeof(double) * n, hipMemcpyDeviceToDevice, s),
-                               "copy") ||
-                        !put_coef(&invh, 1) ||
-                        !check(launch_combine(V + (size_t)(j + 1) * n, 0.0, V + (size_t)(j + 1) * n, coef, 1, n, nullptr, s),
-                               "scale"))
-                        break;
+                    if (!check(launch_combine(V + (size_t)(j + 1) * n, 0.0, w, &invh, 1, n, nullptr, s), "scale")) break;
                 }
                 // Givens rotations on column j
                 for (int i = 0; i < j; ++i) {
@@ -145,12 +138,12 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
                 for (int k = i + 1; k < j; ++k) acc -= H[(size_t)i * m + k] * y[k];
                 y[i] = acc / H[(size_t)i * m + i];
             }
-            if (!put_coef(y.data(), j) || !check(launch_combine(x, 1.0, V, coef, j, n, diag, s), "update")) break;
+            if (!check(launch_combine(x, 1.0, V, y.data(), j, n, diag, s), "update")) break;
             // true residual b - A x for the restart (and the final report)
             if (!apply(x, w)) break;
             const double minus1 = -1.0;
             if (!check(hipMemcpyAsync(V, b, sizeof(double) * n, hipMemcpyDeviceToDevice, s), "copy") ||
-                !put_coef(&minus1, 1) || !check(launch_combine(V, 1.0, w, coef, 1, n, nullptr, s), "residual"))
+                !check(launch_combine(V, 1.0, w, &minus1, 1, n, nullptr, s), "residual"))
                 break;
             double rr = 0.0;
             if (!dots(V, 1, V, &rr)) break;
@@ -170,7 +163,6 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
     if (t) (void)hipFree(t);
     if (diag) (void)hipFree(diag);
     if (partial) (void)hipFree(partial);
-    if (coef) (void)hipFree(coef);
     if (h_partial) (void)hipHostFree(h_partial);
     return rc;
 }
@@ -187,8 +179,8 @@ int solve_refined(bemc_handle h, const Elements& el, const double* b, double* x,
     constexpr double kInnerTol = 1e-6;
     constexpr int kMaxOuter = 20;
     const int64_t n = el.ne;
-    const int kDotBlocks = 256;
-    double *r = nullptr, *d = nullptr, *ax = nullptr, *coef = nullptr, *partial = nullptr, *h_partial = nullptr;
+    const int kDotBlocks = dot_blocks(n);
+    double *r = nullptr, *d = nullptr, *ax = nullptr, *partial = nullptr, *h_partial = nullptr;
     int rc = BEMC_OK;
     auto check = [&](hipError_t e, const char* what) {
         if (e != hipSuccess && rc == BEMC_OK) {
@@ -200,7 +192,6 @@ int solve_refined(bemc_handle h, const Elements& el, const double* b, double* x,
     if (hipMalloc(reinterpret_cast<void**>(&r), sizeof(double) * n) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&d), sizeof(double) * n) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&ax), sizeof(double) * n) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&coef), sizeof(double)) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&partial), sizeof(double) * kDotBlocks) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&h_partial), sizeof(double) * kDotBlocks, hipHostMallocDefault) !=
             hipSuccess) {
@@ -221,8 +212,7 @@ int solve_refined(bemc_handle h, const Elements& el, const double* b, double* x,
     };
     // y = y + c v
     auto axpy = [&](double* y, double c, const double* v) {
-        return check(hipMemcpyAsync(coef, &c, sizeof(double), hipMemcpyHostToDevice, s), "copy") &&
-               check(hipStreamSynchronize(s), "sync") && check(launch_combine(y, 1.0, v, coef, 1, n, nullptr, s), "axpy");
+        return check(launch_combine(y, 1.0, v, &c, 1, n, nullptr, s), "axpy");
     };
     int products = 0, outer = 0;
     double bnorm = 0.0, rnorm = 0.0;
@@ -269,7 +259,6 @@ int solve_refined(bemc_handle h, const Elements& el, const double* b, double* x,
     if (r) (void)hipFree(r);
     if (d) (void)hipFree(d);
     if (ax) (void)hipFree(ax);
-    if (coef) (void)hipFree(coef);
     if (partial) (void)hipFree(partial);
     if (h_partial) (void)hipHostFree(h_partial);
     return rc;
