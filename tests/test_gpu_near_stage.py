@@ -26,7 +26,7 @@ def check(phi, F, ref):
     assert np.max(np.sum(np.abs(F - ref["E"]), axis=1) / ref["abs_E"]) <= TOL
 
 
-@pytest.mark.parametrize("n", [1, 3, 60, 640, 800])
+@pytest.mark.parametrize("n", [1, 3, 60, 250, 500, 640, 800])
 def test_list_lengths(n):
     """A few to about 50,000 pairs: below and above the short-list length, leaf counts exact."""
     w = W.cylinder_workload(40, 30, 1200, n_points=10, near_frac=0.0, seed=3)
