@@ -181,6 +181,9 @@ struct CombineCoef { double c[kMaxCombine]; };
 // c: k <= kMaxCombine coefficients in host memory, copied into the launch
 hipError_t launch_combine(double* y, double a, const double* V, const double* c, int k, int64_t n, const double* d,
                           hipStream_t s);
+// h[j] = sum of partial[j][blocks] of launch_multi_dot, y -= sum_j h[j] V[j] (1 <= k <= kMaxCombine)
+hipError_t launch_project(double* y, const double* V, const double* partial, int blocks, int k, int64_t n, double* h,
+                          hipStream_t s);
 hipError_t launch_divide(double* y, const double* x, const double* d, int64_t n, hipStream_t s);
 
 // workgroups per resident slot that element splitting aims for (dispatcher load balance)

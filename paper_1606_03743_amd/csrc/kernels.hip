@@ -2872,6 +2872,29 @@ __global__ void combine_kernel(double* __restrict__ y, double a, const double* _
     y[i] = a == 0.0 ? s : fma(a, y[i], s);  // (a = 0: y need not hold numbers yet)
 }
 
+// h[j] = sum over b of partial[j][b] (in that order), y -= sum_j h[j] V[j]: a Gram-Schmidt pass whose
+// coefficients need not go through the host (a copy, a wait and a launch that finds the GPU idle, about
+// 25 us between two products of 165 us).  Every workgroup forms all h, a thread each; k <= 256.
+__global__ void project_kernel(double* __restrict__ y, const double* __restrict__ V, const double* __restrict__ partial,
+                               int blocks, int k, int64_t n, double* __restrict__ h)
+{
+    __shared__ double c[kMaxCombine];
+    if (threadIdx.x < k) {
+        double acc = 0.0;
+#pragma unroll 4
+        for (int b = 0; b < blocks; ++b) acc += partial[(int64_t)threadIdx.x * blocks + b];
+        c[threadIdx.x] = -acc;
+        if (blockIdx.x == 0) h[threadIdx.x] = acc;
+    }
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    double s = 0.0;
+#pragma unroll 4
+    for (int j = 0; j < k; ++j) s = fma(c[j], V[(int64_t)j * n + i], s);
+    y[i] += s;
+}
+
 // y[i] = x[i] / d[i]
 __global__ void divide_kernel(double* __restrict__ y, const double* __restrict__ x, const double* __restrict__ d, int64_t n)
 {
@@ -2934,6 +2957,15 @@ hipError_t launch_combine(double* y, double a, const double* V, const double* c,
     CombineCoef coef;
     for (int j = 0; j < k; ++j) coef.c[j] = c[j];
     combine_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(y, a, V, coef, k, n, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_project(double* y, const double* V, const double* partial, int blocks, int k, int64_t n, double* h,
+                          hipStream_t s)
+{
+    if (n <= 0 || k < 1) return hipSuccess;
+    if (k > kMaxCombine) return hipErrorInvalidValue;
+    project_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(y, V, partial, blocks, k, n, h);
     return hipGetLastError();
 }
 

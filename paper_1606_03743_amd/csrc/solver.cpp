@@ -28,7 +28,7 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
     const auto t_start = clock::now();
     const int64_t n = el.ne;
     const int kDotBlocks = dot_blocks(n);
-    double *V = nullptr, *w = nullptr, *t = nullptr, *diag = nullptr, *partial = nullptr;
+    double *V = nullptr, *w = nullptr, *t = nullptr, *diag = nullptr, *partial = nullptr, *column = nullptr;
     double* h_partial = nullptr;
     int rc = BEMC_OK;
     auto check = [&](hipError_t e, const char* what) {
@@ -38,16 +38,22 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
         }
         return rc == BEMC_OK;
     };
-    if (hipMalloc(reinterpret_cast<void**>(&V), sizeof(double) * (size_t)(m + 1) * n) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&w), sizeof(double) * n) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&t), sizeof(double) * n) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&diag), sizeof(double) * n) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&partial), sizeof(double) * (size_t)(m + 1) * kDotBlocks) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&h_partial), sizeof(double) * (size_t)(m + 1) * kDotBlocks,
+    // one allocation: V[m + 1][n], w, t, diag, the dots' partial sums, and a column of H as the two
+    // Gram-Schmidt passes' coefficients and the partial sums of |w|^2
+    const size_t n_partial = (size_t)(m + 1) * kDotBlocks, n_column = 2 * (size_t)(m + 1) + kDotBlocks;
+    if (hipMalloc(reinterpret_cast<void**>(&V), sizeof(double) * ((size_t)(m + 4) * n + n_partial + n_column)) !=
+            hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&h_partial), sizeof(double) * std::max(n_partial, n_column),
                       hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         err = "solver workspace";
         rc = BEMC_E_OUT_OF_MEMORY;
+    } else {
+        w = V + (size_t)(m + 1) * n;
+        t = w + n;
+        diag = t + n;
+        partial = diag + n;
+        column = partial + n_partial;
     }
     // <V_j, v> for j < k, summed on the host in fixed order
     auto dots = [&](const double* Vb, int k, const double* v, double* out) {
@@ -83,7 +89,7 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
         bnorm = std::sqrt(bnorm);
         res = bnorm;
         converged = bnorm == 0.0;
-        std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m), hcol(m + 1), h2(m + 1);
+        std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m);
         double beta = bnorm;  // V[0] holds the unnormalised residual
         while (!converged && rc == BEMC_OK && products < max_iter) {
             const double inv = 1.0 / beta;
@@ -94,17 +100,22 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
             for (; j < m && products < max_iter; ++j) {
                 // w = A D^-1 v_j
                 if (!check(launch_divide(t, V + (size_t)j * n, diag, n, s), "precond") || !apply(t, w)) break;
-                // two passes of classical Gram-Schmidt against v_0 .. v_j
-                if (!dots(V, j + 1, w, hcol.data())) break;
-                for (int i = 0; i <= j; ++i) hcol[i] = -hcol[i];
-                if (!check(launch_combine(w, 1.0, V, hcol.data(), j + 1, n, nullptr, s), "axpy")) break;
-                if (!dots(V, j + 1, w, h2.data())) break;
-                for (int i = 0; i <= j; ++i) h2[i] = -h2[i];
-                if (!check(launch_combine(w, 1.0, V, h2.data(), j + 1, n, nullptr, s), "axpy")) break;
+                // two passes of classical Gram-Schmidt against v_0 .. v_j and |w|^2, read back once
+                const int k = j + 1;
+                double *h1 = column, *h2 = column + k, *nn = column + 2 * k;
+                if (!check(launch_multi_dot(V, k, n, w, partial, kDotBlocks, s), "dot") ||
+                    !check(launch_project(w, V, partial, kDotBlocks, k, n, h1, s), "project") ||
+                    !check(launch_multi_dot(V, k, n, w, partial, kDotBlocks, s), "dot") ||
+                    !check(launch_project(w, V, partial, kDotBlocks, k, n, h2, s), "project") ||
+                    !check(launch_multi_dot(w, 1, n, w, nn, kDotBlocks, s), "dot") ||
+                    !check(hipMemcpyAsync(h_partial, column, sizeof(double) * (2 * (size_t)k + kDotBlocks),
+                                          hipMemcpyDeviceToHost, s), "copy") ||
+                    !check(hipStreamSynchronize(s), "sync"))
+                    break;
                 double hn = 0.0;
-                if (!dots(w, 1, w, &hn)) break;
+                for (int b = 0; b < kDotBlocks; ++b) hn += h_partial[2 * k + b];
                 hn = std::sqrt(hn);
-                for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = -(hcol[i] + h2[i]);
+                for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = h_partial[i] + h_partial[k + i];
                 H[(size_t)(j + 1) * m + j] = hn;
                 if (hn > 0.0) {
                     const double invh = 1.0 / hn;
@@ -159,10 +170,6 @@ int solve_gmres(bemc_handle h, const Elements& el, const double* b, double* x, d
         info->seconds = std::chrono::duration<double>(clock::now() - t_start).count();
     }
     if (V) (void)hipFree(V);
-    if (w) (void)hipFree(w);
-    if (t) (void)hipFree(t);
-    if (diag) (void)hipFree(diag);
-    if (partial) (void)hipFree(partial);
     if (h_partial) (void)hipHostFree(h_partial);
     return rc;
 }

@@ -41,3 +41,24 @@ def test_product(kind, n_rhs, precision, tol):
     for r in (0, n_rhs - 1):
         ref = oracle.evaluate(tri, rect, sigma[r], cen, oracle.params(33, 7), with_abs=True)
         assert np.max(np.abs(got[r, rows] - ref["phi"]) / ref["abs_phi"]) <= tol
+
+
+@pytest.mark.parametrize("shape, restart", [((9, 7, 27), 200), ((8, 16, 64), 5), ((24, 20, 240), 13), ((50, 60, 1000), 200)])
+def test_solver_projections(shape, restart):
+    """Elements below, at and above a workgroup of the projection, one and several partial sums of
+    the dot products, short and long bases: the residual that the solver reports is the product's."""
+    import torch
+
+    half = 2.0 * np.pi * shape[1] / shape[0]  # rectangles twice as high as wide
+    tri, rect = W.cylinder(1.0, -half, half, *shape)
+    ctx = bemc.Context(0)
+    ctx.upload_geometry(tri, rect)
+    b = torch.full((len(tri) + len(rect),), 3.0, dtype=torch.float64, device="cuda:0")
+    sigma, info = ctx.solve(b, tol=1e-10, max_iter=600, restart=restart)
+    again, _ = ctx.solve(b, tol=1e-10, max_iter=600, restart=restart)
+    r = (b - ctx.collocation(sigma[None])[0]).norm() / b.norm()
+    ctx.close()
+    assert info["converged"] == 1
+    # both residuals are formed from the same densities; the sums round at 1e-15
+    assert abs(float(r) - info["rel_residual"]) <= 1e-13 and float(r) <= 1.001e-10
+    assert torch.equal(again, sigma)
