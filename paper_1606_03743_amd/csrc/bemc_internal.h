@@ -116,6 +116,7 @@ struct FarArgs {
     DevCounters* ctr;
     int dr_rules;            // 1: per-pair rule choice by distance ratio (levels below)
     LevelRules lv;
+    int beside;              // 1: leave room on the CUs for other streams' kernels (served batches)
 };
 
 struct NearArgs {

@@ -157,9 +157,9 @@ __device__ __forceinline__ void wave_lds_sync()
 // when another 64 pairs might not fit.  Appending each candidate's pairs with an atomic of its
 // own bound the pass: they all hit one address (32,768 points x 150,000 elements, 697,000 pairs:
 // see near_list_kernel).  Called with every lane of the wavefront active.
-constexpr unsigned kListBuf = 512;
+template <unsigned SIZE>
 struct NearBuffer {
-    NearPair* buf;  // [kListBuf]
+    NearPair* buf;  // [SIZE]
     unsigned n;     // pairs held (the same in every lane)
 
     __device__ __forceinline__ void flush(NearPair* list, unsigned long long cap, DevCounters* ctr)
@@ -181,7 +181,7 @@ struct NearBuffer {
         if (m == 0ull) return;
         if (is_near) buf[n + lanes_below(m)] = NearPair{ p, e };
         n += (unsigned)__popcll(m);
-        if (n > kListBuf - 64) flush(list, cap, ctr);
+        if (n > SIZE - 64) flush(list, cap, ctr);
     }
 };
 
@@ -274,6 +274,10 @@ constexpr int kListPPT = 2;
 constexpr int kListPoints = kBlock * kListPPT;
 constexpr int64_t kListFine = 1024;  // elements of a chunk from which the points' own boxes pay
 
+// FINE: with the points' own boxes, for long chunks (a short chunk's candidates are tested at once:
+// forming the boxes takes longer, 30 us).  Without them the kernel needs few enough registers and little
+// enough LDS to run beside another stream's far kernel, which a served batch of few points has to.
+template <bool FINE>
 __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restrict__ pts, int64_t n, Elements el,
                                                            NearPair* __restrict__ list, unsigned long long cap,
                                                            DevCounters* __restrict__ ctr, int64_t chunk)
@@ -283,14 +287,13 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
     __shared__ uint32_t cand[kBlock];
     __shared__ double4 cand_c[kBlock];  // the candidates' centroids and thresholds
     __shared__ int ncand;
+    constexpr unsigned kListBuf = FINE ? 512 : 256;
     __shared__ NearPair pairs[kBlock / 64][kListBuf];
     const int64_t ne = el.ne;
     double x[kListPPT], y[kListPPT], z[kListPPT];
     bool valid[kListPPT];
     uint32_t idx[kListPPT];
     double lo[3] = { INFINITY, INFINITY, INFINITY }, hi[3] = { -INFINITY, -INFINITY, -INFINITY };
-    // a short chunk's candidates are tested at once: forming the boxes takes longer (30 us)
-    const bool fine = chunk > kListFine;
     Box part[kListPPT][2];
 #pragma unroll
     for (int k = 0; k < kListPPT; ++k) {
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
             lo[0] = fmin(lo[0], x[k]); lo[1] = fmin(lo[1], y[k]); lo[2] = fmin(lo[2], z[k]);
             hi[0] = fmax(hi[0], x[k]); hi[1] = fmax(hi[1], y[k]); hi[2] = fmax(hi[2], z[k]);
         }
-        if (fine) {
+        if constexpr (FINE) {
             const double e0 = valid[k] ? 0.0 : INFINITY;
             split_boxes(Box{ { x[k] + e0, y[k] + e0, z[k] + e0 }, { x[k] - e0, y[k] - e0, z[k] - e0 } }, part[k][0],
                         part[k][1]);
@@ -329,7 +332,7 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
         box[threadIdx.x] = v;
     }
     __syncthreads();
-    NearBuffer near{ pairs[wave], 0u };
+    NearBuffer<kListBuf> near{ pairs[wave], 0u };
     const Box all{ { box[0], box[1], box[2] }, { box[3], box[4], box[5] } };
     // this workgroup's chunk of the elements (blockIdx.y)
     const int64_t e_begin = (int64_t)blockIdx.y * chunk, e_end = min(ne, e_begin + chunk);
@@ -359,7 +362,7 @@ __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restr
                 const double4 cc = cand_c[i0 + lane_id()];
 #pragma unroll
                 for (int k = 0; k < kListPPT; ++k)
-                    mine[k] = !fine || part[k][0].in_reach(cc.x, cc.y, cc.z, cc.w) || part[k][1].in_reach(cc.x, cc.y, cc.z, cc.w);
+                    mine[k] = !FINE || part[k][0].in_reach(cc.x, cc.y, cc.z, cc.w) || part[k][1].in_reach(cc.x, cc.y, cc.z, cc.w);
             }
 #pragma unroll
             for (int k = 0; k < kListPPT; ++k)
@@ -2569,14 +2572,23 @@ __global__ void zero_counters_kernel(DevCounters* c)
     if (i < (int)(sizeof(DevCounters) / sizeof(unsigned long long))) w[i] = 0ull;
 }
 
+// LDS of a workgroup from which four, not five, fit a CU (160 KB), and leave 30 KB
+constexpr size_t kBesideLds = 33280;
+
 template <bool DR, int NT, int NR, int T1, int T2, int T3, int R1, int R2, int R3, bool MIXED, int PPT, int MODE>
 hipError_t far_eval_launch(const FarArgs& a, hipStream_t s)
 {
+    // Batches of other streams run beside a served one: five workgroups of the mixed kernel with one point per
+    // lane (90 registers) would leave a CU 32 registers per lane, and the list pass (62) and the near
+    // kernel (120) of a short batch would wait for its workgroups to end, each some milliseconds
+    // long; four leave 128 (120 queries, 1,000,000 elements: p50 91 ms with five, 31 with four).
+    using Tile = TileLds<MIXED, 1, !MIXED && PPT == 1 && MODE != kFarGrad>;
+    const size_t spare = a.beside && MIXED && PPT == 1 && sizeof(Tile) < kBesideLds ? kBesideLds - sizeof(Tile) : 0;
     const int64_t per = (int64_t)kBlock * PPT;
     const int64_t blocks = (a.n + per - 1) / per;
     if (blocks > 0x7fffffff || a.n_split < 1 || a.n_split > 65535) return hipErrorInvalidValue;
     far_eval_kernel<DR, NT, NR, T1, T2, T3, R1, R2, R3, MIXED, PPT, MODE>
-        <<<dim3((unsigned)blocks, (unsigned)a.n_split), dim3(kBlock), 0, s>>>(a);
+        <<<dim3((unsigned)blocks, (unsigned)a.n_split), dim3(kBlock), spare, s>>>(a);
     return hipGetLastError();
 }
 
@@ -2781,7 +2793,9 @@ hipError_t launch_near_list(const double* pts, int64_t n, const Elements& el, Ne
     const int64_t split = std::max<int64_t>(1, std::min<int64_t>({ (2048 + blocks - 1) / blocks, units, 65535 }));
     const int64_t chunk = ((units + split - 1) / split) * 16;
     const int64_t chunks = (el.ne + chunk - 1) / chunk;
-    near_list_kernel<<<dim3((unsigned)blocks, (unsigned)chunks), kBlock, 0, s>>>(pts, n, el, list, cap, ctr, chunk);
+    const dim3 grid((unsigned)blocks, (unsigned)chunks);
+    if (chunk > kListFine) near_list_kernel<true><<<grid, kBlock, 0, s>>>(pts, n, el, list, cap, ctr, chunk);
+    else near_list_kernel<false><<<grid, kBlock, 0, s>>>(pts, n, el, list, cap, ctr, chunk);
     return hipGetLastError();
 }
 

@@ -407,6 +407,7 @@ bool Server::launch(Slot& s, std::string& err)
     fa.n = n;
     fa.rhs = 0;
     fa.n_out = 4;
+    fa.beside = 1;
     fa.n_rhs = 1;
     fa.K = K;
     fa.phi = s.d_far;
