@@ -284,7 +284,7 @@ def main():
     achieved = alg_flops / far_avg_s / 1e12
     traffic = traffic_from_profile("far_fp64")
     counted = counted_flops_from_profile("far_fp64")
-    prof_ms = trace_avg_ms("far_eval_kernel<false, 33, 49, 0, 0, 0, 0, 0, 0, false, 3, false>")
+    prof_ms = trace_avg_ms("far_eval_kernel<false, 33, 49, 0, 0, 0, 0, 0, 0, false, 3, 0>")
     out = {
         "metric": "element-fieldpoint interactions/s (phi+E) FP64 vs mixed @1e-6; p99 query ms",
         "value": value,

@@ -73,7 +73,8 @@ extern "C" {
                         root), per-element partial sums scaled by
                         the element charge and accumulated per field point in FP64; the
                         distance-ratio classification, the near field and on-element
-                        integrals stay FP64 */
+                        integrals stay FP64, and so do evaluations of at most 128
+                        points */
 #define BEMC_MIXED_REFINE 2 /* bemc_solve_densities only: corrections solved with mixed
                                products, residuals formed with FP64 products (iterative
                                refinement), so FP64 tolerances are reachable */
@@ -173,12 +174,15 @@ int bemc_upload_densities(bemc_handle h, const double* sigma, int n_rhs, int sig
  * The call enqueues on `stream` the near-pair list (every pair with D < near_dr L, by a
  * classification pass), the far-field kernel (point-charge sums of the other pairs) and the
  * FP64 near field, and returns without waiting for them.  With a growing near-pair list
- * (the default, see bemc_set_near_capacity) the host reads the list pass's pair count --
- * a wait of about a millisecond, while the far field is already queued behind it -- and,
- * if the list was too short, grows it and repeats the list pass (never the far field)
- * before it enqueues the near field.  With a fixed list there is no host wait at all.
+ * (the default, see bemc_set_near_capacity) that could not hold every pair of the call the
+ * host reads the list pass's pair count -- a wait of about a millisecond, while the far
+ * field is already queued behind it -- and, if the list was too short, grows it and repeats
+ * the list pass (never the far field) before it enqueues the near field.  With a list of n
+ * times the number of elements, or a fixed one, there is no host wait at all.
  * Results are reproducible bit for bit: far-field chunks are added in fixed order, and
- * each point's near pairs are summed in element order.  A field point lying on an
+ * each point's near pairs are summed in an order that their element indices set.  The
+ * potential alone (E = NULL) has kernels of its own; it agrees with the one computed
+ * beside the field to rounding.  A field point lying on an
  * element gets the principal-value field there; bemc_query_stats then returns
  * BEMC_W_ON_SURFACE.  Consecutive calls on one context may use different streams (each
  * call waits on the device for the previous one).
@@ -198,8 +202,9 @@ int bemc_eval(bemc_handle h, const double* pts, int64_t n, int precision, int rh
  * at once) and 524288 near pairs (D < near_dr L) per call; more near pairs leave the near
  * field incomplete and are reported, as for a fixed list of bemc_set_near_capacity, by
  * bemc_query_stats and the next evaluation call (BEMC_E_LIMIT).  The element-chunk split
- * of the far field is capped by the array (results then differ from bemc_eval's in
- * summation grouping only, at rounding level).  All contexts on one GPU share that GPU's
+ * of the far field is capped by the array, and the potential alone comes from the field's
+ * kernels (results then differ from bemc_eval's in summation grouping only, at rounding
+ * level).  All contexts on one GPU share that GPU's
  * array, which keeps the last call's contents: calls on one context are ordered (each
  * waits on the device for the previous one), but calls from different contexts on one
  * GPU that overlap on the device race -- the caller serialises them (one stream, or

@@ -5,10 +5,11 @@
 // pairs are regrouped by field point (counts per point, an exclusive scan, a scatter) and
 // each point's segment is ordered by element index.  The near kernel walks the pairs in
 // the list's order (neighbouring points and the same element: similar subdivision trees
-// side by side) and writes each pair's result record to its slot; one thread per point
-// then adds its segment in element order to the point's far-field result.  The outcome
-// does not depend on how the GPU scheduled the work.  No step needs the pair count on the
-// host: the kernels read it from the device counters.
+// side by side) and writes each pair's result record to its slot; the last kernel then adds
+// each point's segment, in an order fixed by the slots, to the point's far-field result.  The
+// outcome does not depend on how the GPU scheduled the work.  Small evaluations take kernels
+// of fewer launches with the same slots (order_small_kernel, finish_few_kernel).  No step needs
+// the pair count on the host: the kernels read it from the device counters.
 //
 // The near kernel's lanes take pairs from a shared cursor, most expensive first: a pair's
 // subdivision has a number of leaves that grows with log2(L / d), d the distance from the
@@ -219,8 +220,8 @@ __device__ __forceinline__ double triangle_distance2(const double (&p)[3], const
 
 // Cost class of a near pair (higher = more subdivision leaves expected): 4 steps per octave of
 // L / d, d the distance from the point to the element (its closest point), the costliest step
-// where d vanishes without the point lying on the element.  Deep pairs (d <= L / 16: a near
-// region at some five levels or more) come first, walked by a wavefront each; then the
+// where d vanishes without the point lying on the element.  Deep pairs (d <= L / 4: a near
+// region at some three levels or more) come first, walked by a wavefront each; then the
 // others.  Rectangles come before triangles in each group: the near kernel's wavefronts take
 // windows of the order far apart in time, and a wavefront whose lanes mix both kinds runs
 // both rule loops.
