@@ -27,7 +27,9 @@ namespace bemc {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int64_t kFinishFew = 65536;  // rows x points below which a thread per result does not fill the GPU
+// rows of partial sums x points below which a thread per result does not fill the GPU (the rows that the
+// evaluation sums, not those the caller asks for: the potential is the same with and without the field)
+constexpr int64_t kFinishFew = 65536;
 
 __device__ __forceinline__ unsigned long long pair_total(const DevCounters* ctr, unsigned long long cap)
 {
@@ -549,7 +551,7 @@ hipError_t near_finish(const NearWork& w, int64_t n, int mode, int rows, const d
     if (mode == kNearColloc) return hipErrorInvalidValue;
     const int rec = mode == kNearGrad ? 6 : (mode == kNearPhi ? 1 : 4);
     const int64_t threads = (int64_t)rows * n;
-    if (threads < kFinishFew) {
+    if ((int64_t)prow * n < kFinishFew) {
         const int P = n <= 32 ? 1 : 8;  // (a row's neighbouring points share the lines of memory read)
         const int64_t waves = (n + P - 1) / P * rows;
         const unsigned blocks = (unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
