@@ -2144,29 +2144,34 @@ __device__ __forceinline__ bool advance_within(NearState& s, int root)
     return false;
 }
 
-// One lane walks the subtree below the near node s (above the depth cap) depth first.
+// One lane walks the subtree below the near node s (above the depth cap) depth first and returns
+// the nodes it visited.  It stops at its first leaf past `budget` visits, what the visit limit
+// leaves of its pair's: a near limit of thousands has subtrees of billions of nodes.
 template <int MODE>
-__device__ void walk_subtree(NearState s, const NearGeom& g, double p1, double p2, double p3, double thr2,
-                             int max_depth, const double4* __restrict__ tri_nodes,
-                             const double4* __restrict__ rect_nodes, int nt, int nr, double (&acc)[7],
-                             unsigned long long& n_leaves, unsigned long long& n_cap, int& max_level)
+__device__ int walk_subtree(NearState s, const NearGeom& g, double p1, double p2, double p3, double thr2,
+                            int max_depth, int budget, const double4* __restrict__ tri_nodes,
+                            const double4* __restrict__ rect_nodes, int nt, int nr, double (&acc)[7],
+                            unsigned long long& n_leaves, unsigned long long& n_cap, int& max_level)
 {
     const int root = s.level;
+    int visits = 0;
     to_child(s, 0);
     while (true) {
         double h;
         NodeGeom nd;
         const bool near = visit_node(s, g, p1, p2, p3, thr2, h, nd);
+        ++visits;
         if (s.level > max_level) max_level = s.level;
-        if (near && s.level < max_depth) {
+        if (near && s.level < max_depth && visits <= budget) {
             to_child(s, 0);
             continue;
         }
         leaf_add<MODE>(s.kind, g, p1, p2, p3, nd, h, tri_nodes, rect_nodes, nt, nr, acc);
         n_leaves++;
         if (near) n_cap++;
-        if (!advance_within(s, root)) break;
+        if (visits > budget || !advance_within(s, root)) break;
     }
+    return visits;
 }
 
 // A pair with a deep subdivision (the leading cost classes; every pair of a short list), walked by
@@ -2177,8 +2182,8 @@ __device__ void walk_subtree(NearState s, const NearGeom& g, double p1, double p
 // around its foot), so its depth-first walk would take thousands of visits in one lane.
 // Each lane sums its leaves in a fixed order; the lanes' sums are added by a fixed butterfly,
 // so results are reproducible.  More near nodes in a level than kFront: the lane that found
-// one walks its subtree depth first itself.  The visit limit ends the walk after the level in
-// which the pair's visits pass it.
+// one walks its subtree depth first itself.  The visit limit ends the walk after the level, or
+// after the single lanes' subtrees, with which the pair's visits pass it.
 template <int MODE, typename NearLds>
 __device__ void heavy_pair(const NearArgs& a, unsigned long long w, NearLds& q, const double4* __restrict__ tri_nodes, const double4* __restrict__ rect_nodes, int nt,
                            int nr, int lane, unsigned long long& n_leaves, unsigned long long& n_cap,
@@ -2292,9 +2297,18 @@ __device__ void heavy_pair(const NearArgs& a, unsigned long long w, NearLds& q, 
         nq += (int)__popcll(lm);
         base += 64;
         wave_lds_sync();
-        if (spill)
-            walk_subtree<MODE>(s, g, p1, p2, p3, thr2, a.max_depth, tri_nodes, rect_nodes, nt, nr, acc, n_leaves,
-                               n_cap, max_level);
+        if (lane_mask(spill) != 0ull) {
+            int walked = 0;
+            if (spill)
+                walked = walk_subtree<MODE>(s, g, p1, p2, p3, thr2, a.max_depth, (int)(a.visit_limit - visits), tri_nodes,
+                                            rect_nodes, nt, nr, acc, n_leaves, n_cap, max_level);
+            for (int o = 32; o > 0; o >>= 1) walked += __shfl_xor(walked, o);  // (64 x 2^22 at most)
+            visits += walked;
+            if (visits > a.visit_limit) {
+                if (lane == 0) n_limit++;
+                done = true;
+            }
+        }
     }
     wave_lds_sync();  // the queue and the levels are reused by the next pair
     // the lanes' sums added by a fixed butterfly (every lane ends with the same total)
@@ -2308,8 +2322,9 @@ __device__ void heavy_pair(const NearArgs& a, unsigned long long w, NearLds& q, 
 // vectors), kNearGrad (field gradient at field points; NaN for a point on its element).
 // The depth-first variant is held to four wavefronts per SIMD (128 registers): its workgroups
 // then fit beside another stream's running far kernel (left alone the compiler takes 157).
+// The field's other variant is held to three (left alone it takes 217 registers: two).
 template <int MODE, bool DEEP>
-__global__ __launch_bounds__(kBlock, DEEP ? 1 : 4) void near_kernel(NearArgs a)
+__global__ __launch_bounds__(kBlock, !DEEP ? 4 : (MODE == kNearEval ? 3 : 1)) void near_kernel(NearArgs a)
 {
     // the walks: the leading entries of the order (the points lying on their element follow);
     // the first `heavy` of them have deep subdivisions (DEEP: walked breadth first, a wavefront
