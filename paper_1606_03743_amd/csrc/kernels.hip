@@ -687,7 +687,7 @@ __device__ __forceinline__ float inv_cube_phi(float w, float x, float& phi)
 //              points x 150,000 elements, 33-point / 7 x 7, FP64: 73.0 -> 53.9 ms; mixed, 50,001 x
 //              18,000: 17.8 -> 11.9 ms).  FP32: r^2 is taken
 //              over D^2 (grad_base), so that no power of a length above the square appears in
-//              single precision, whatever the geometry's unit.
+//              single precision: sizes down to 1e-18 and up to 1e18 of the geometry's unit.
 template <int PPT, typename T>
 __device__ __forceinline__ T grad_base(const Local<PPT, T>& L, int k, T g)  // D^2 + g, or over D^2
 {
@@ -1166,7 +1166,7 @@ __device__ __forceinline__ void add_element(PointSet<PPT, MODE>& P, int k, doubl
             s3 = S5 + fma(L.q1[k], Sa, fma(L.q2[k], Sb, Sg));
             Sa *= ri0; Sb *= ri0; Saa *= t; Sab *= t;
             d[0] *= ri0; d[1] *= ri0; d[2] *= ri0;
-            q *= (double)(ri0 * t);
+            q *= (double)ri0 * (double)t;  // (1/D^3 would leave FP32's range below 1e-13 of a unit)
         }
         const T f1[3] = { s.fr[0][j], s.fr[1][j], s.fr[2][j] }, f2[3] = { s.fr[3][j], s.fr[4][j], s.fr[5][j] };
         double out[6];
