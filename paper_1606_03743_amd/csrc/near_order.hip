@@ -381,7 +381,64 @@ __global__ void scatter_kernel(const NearPair* __restrict__ list, const DevCount
 // The whole ordering of a short list of few points in one launch of one workgroup: cost classes and
 // per-point counts, their starts, both scatters, the ranks (as the kernels above; five launches of
 // a few microseconds each otherwise, on the GPU and in the host's enqueueing).
+// Ranks of a point's k pairs among each other: by comparing each with all (k^2 reads of L1), or,
+// for long segments, from a bit per element set in LDS and the set bits below each (linear, but a
+// handful of barriers per point and kRankBits elements).  The comparisons alone took 95 of 107 ms of a
+// near stage of 256 points with 1,955 pairs each (long strips).
 constexpr int kSmallBlock = 1024;
+constexpr int kRankWords = 4 * kSmallBlock;        // 32 KB with the words' prefix sums
+constexpr uint32_t kRankBits = 32 * kRankWords;    // 131,072 elements at a time
+// pairs of a point beyond which the bits are faster, squared, per kRankBits elements
+constexpr uint64_t kRankCompare = 128 * 128;
+
+// The slots of a point's pairs grouped[s .. s + k) by rank, by the whole workgroup (every thread calls it).
+__device__ __forceinline__ void rank_by_bits(const NearPair* grouped, const uint32_t* origin, uint32_t s, uint32_t k,
+                                             uint32_t ne, uint32_t* bits, uint32_t* below, uint32_t* wave_total,
+                                             uint32_t* __restrict__ slot)
+{
+    constexpr int kPer = kRankWords / kSmallBlock, kWaves = kSmallBlock / 64;
+    const int t = threadIdx.x;
+    uint32_t base = s;  // the slot of the range's first pair
+    for (uint32_t e0 = 0; e0 < ne; e0 += kRankBits) {  // (ne < 2^31: no wrap)
+        for (int w = t; w < kRankWords; w += kSmallBlock) bits[w] = 0u;
+        __syncthreads();
+        for (uint64_t i = t; i < k; i += kSmallBlock) {
+            const uint32_t d = grouped[s + i].elem - e0;  // (wraps past kRankBits for earlier elements)
+            if (d < kRankBits) atomicOr(&bits[d >> 5], 1u << (d & 31u));
+        }
+        __syncthreads();
+        // the set bits of the words before each: kPer words a thread, the wavefronts' totals in LDS
+        uint32_t own[kPer], sum = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            own[j] = sum;
+            sum += __popc(bits[kPer * t + j]);
+        }
+        uint32_t inc = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t v = __shfl_up(inc, o);
+            if ((t & 63) >= o) inc += v;
+        }
+        if ((t & 63) == 63) wave_total[t >> 6] = inc;
+        __syncthreads();
+        uint32_t before = inc - sum, total = 0;
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < (t >> 6)) before += wave_total[w];
+            total += wave_total[w];
+        }
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) below[kPer * t + j] = before + own[j];
+        __syncthreads();
+        for (uint64_t i = t; i < k; i += kSmallBlock) {
+            const uint32_t d = grouped[s + i].elem - e0;
+            if (d < kRankBits)
+                slot[origin[s + i]] = base + below[d >> 5] + __popc(bits[d >> 5] & ((1u << (d & 31u)) - 1u));
+        }
+        base += total;
+        __syncthreads();  // the words are set again
+    }
+}
+
 __global__ __launch_bounds__(kSmallBlock) void order_small_kernel(
     const NearPair* __restrict__ list, const DevCounters* __restrict__ ctr, unsigned long long cap,
     const double* __restrict__ pts, int64_t n, Elements el, uint8_t* cost, uint32_t* __restrict__ buckets,
@@ -393,12 +450,13 @@ __global__ __launch_bounds__(kSmallBlock) void order_small_kernel(
     const int t = threadIdx.x;
     if (t < 2 * kCostClasses) (&hist[0][0])[t] = 0u;
     __syncthreads();
-    const uint32_t total = (uint32_t)pair_total(ctr, cap);
+    __shared__ uint32_t bits[kRankWords], below[kRankWords], wave_total[kSmallBlock / 64];
+    const uint64_t total = pair_total(ctr, cap);
     if (total == 0) {  // (the points' counts are zero already)
         if (t < kCostClasses) buckets[kCostClasses + t] = 0u;
         return;
     }
-    for (uint32_t i = t; i < total; i += kSmallBlock) {
+    for (uint64_t i = t; i < total; i += kSmallBlock) {
         const NearPair pr = list[i];
         const int c = cost_class(pts, n, el, pr);
         cost[i] = (uint8_t)c;
@@ -429,23 +487,33 @@ __global__ __launch_bounds__(kSmallBlock) void order_small_kernel(
         }
     }
     __syncthreads();
-    for (uint32_t i = t; i < total; i += kSmallBlock) {
+    for (uint64_t i = t; i < total; i += kSmallBlock) {
         const NearPair pr = list[i];
         const uint32_t at = atomicAdd(&first[0][cost[i]], 1u);
-        order[at] = i;
+        order[at] = (uint32_t)i;
         opair[at] = pr;
         const uint32_t pos = atomicAdd(&first[1][pr.point], 1u);
         grouped[pos] = pr;
-        origin[pos] = i;
+        origin[pos] = (uint32_t)i;
     }
     __threadfence_block();
     __syncthreads();
-    for (uint32_t i = t; i < total; i += kSmallBlock) {
+    // (the cursors first[1] stand at their segments' ends)
+    const uint32_t ne = (uint32_t)el.ne;
+    const uint64_t compare = kRankCompare * ((ne + kRankBits - 1) / kRankBits);
+    for (uint64_t i = t; i < total; i += kSmallBlock) {
         const NearPair v = grouped[i];
-        const uint32_t k = hist[1][v.point], s = first[1][v.point] - k;  // (the cursor stands at the segment's end)
+        const uint32_t k = hist[1][v.point], s = first[1][v.point] - k;
+        if ((uint64_t)k * k > compare) continue;
         uint32_t rank = 0;
+#pragma unroll 8
         for (uint32_t j = 0; j < k; ++j) rank += grouped[s + j].elem < v.elem ? 1u : 0u;
         slot[origin[i]] = s + rank;
+    }
+    for (int p = 0; p < (int)n; ++p) {
+        const uint32_t k = hist[1][p];
+        if ((uint64_t)k * k > compare)
+            rank_by_bits(grouped, origin, first[1][p] - k, k, ne, bits, below, wave_total, slot);
     }
 }
 
