@@ -243,7 +243,7 @@ Elements bemc_context::elements() const
 {
     Elements e{};
     e.geom = d_geom; e.cen = d_cen; e.thr2 = d_thr2; e.frame = d_frame; e.loc = d_loc; e.nrec = d_nrec; e.L = d_L;
-    e.area = d_area; e.nrm = d_nrm; e.q = d_q; e.ne = ne; e.n_tri = (int)n_tri; e.n_rhs = n_rhs;
+    e.area = d_area; e.nrm = d_nrm; e.q = d_q; e.near_dr = near_dr; e.ne = ne; e.n_tri = (int)n_tri; e.n_rhs = n_rhs;
     return e;
 }
 

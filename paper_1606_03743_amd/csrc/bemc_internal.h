@@ -57,6 +57,7 @@ struct Elements {
     const double* area;  // [ne]
     const double* nrm;   // [3][ne]  unit normal
     const double* q;     // [n_rhs][ne]  sigma * area
+    double near_dr;      // the thresholds' near_dr
     int64_t ne;
     int n_tri;
     int n_rhs;
@@ -229,6 +230,8 @@ constexpr int kOnElementClass = 0;
 constexpr int kDeepClass = 128;      // first class of the deep pairs
 constexpr int kDeepCost = 24;        // estimated-cost step from which a pair is deep (d <= L / 4; near
                                      // stage of 700,000 pairs 1.33 ms, 1.45 ms at L / 2, 2.35 at L / 16)
+constexpr double kWideNear = 5.0;    // near limits beyond which a level has more near nodes than a wavefront
+constexpr int kDeepCostWide = 32;    // keeps, whose subtrees single lanes walk: deep from L / 16 there
 size_t near_scan_temp_bytes(int64_t n);
 hipError_t near_work_alloc(NearWork& w, int64_t n, unsigned long long pairs, int rows);  // frees w first
 void near_work_free(NearWork& w);

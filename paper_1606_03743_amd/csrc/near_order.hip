@@ -250,7 +250,7 @@ __device__ __forceinline__ int cost_class(const double* __restrict__ pts, int64_
     const double L = el.L[e];
     int c = 63;
     if (d2 > 1e-24 * L * L) c = min(63, max(1, (int)floor(4.0 * (log2(L) - 0.5 * log2(d2)) + 16.0)));
-    return (c >= kDeepCost ? kDeepClass : 0) + (tri ? 0 : 64) + c;
+    return (c >= (el.near_dr > kWideNear ? kDeepCostWide : kDeepCost) ? kDeepClass : 0) + (tri ? 0 : 64) + c;
 }
 
 // Clears the per-class counts and cursors (buckets) and the per-point counts and cursors.
