@@ -1303,6 +1303,9 @@ __device__ __forceinline__ void far_eval_dr_range(const FarArgs& a, Lds& s, Poin
         stage_tile<TRI, MIXED, FR, MODE == kFarField, GRAD>(s, a.el, a.lv.tab, nn, t0, te, a.rhs, 1, nfold, prow, tf,
                                              sum_scale<MODE, T>());
         __syncthreads();
+        // (a wavefront without a point only helps staging: a served batch of 64 points or fewer has three
+        // such of four, and the first test below is true for them)
+        if (n_valid == 0) continue;
         for (int j = 0; j < te; ++j) {
             const double thr2 = s.thr2[j], q = s.q[0][j];
             double D2[PPT];
