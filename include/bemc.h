@@ -74,7 +74,7 @@ extern "C" {
                         the element charge and accumulated per field point in FP64; the
                         distance-ratio classification, the near field and on-element
                         integrals stay FP64, and so do evaluations of at most 128
-                        points */
+                        points (served batches excepted) */
 #define BEMC_MIXED_REFINE 2 /* bemc_solve_densities only: corrections solved with mixed
                                products, residuals formed with FP64 products (iterative
                                refinement), so FP64 tolerances are reachable */
@@ -219,8 +219,8 @@ int bemc_eval_noalloc(bemc_handle h, const double* pts, int64_t n, int precision
  * derivatives of the field follow from the same point charges, e.g. for field maps with
  * Hermite interpolation).  Classification, near-field
  * subdivision, rule choice (including bemc_set_dr_rules) and precision handling are those
- * of bemc_eval; BEMC_MIXED forms the FP32 node sums from unit vectors d/r (no power of 1/r
- * above the third in FP32).  A field point lying on an element gets NaN in all six rows
+ * of bemc_eval; BEMC_MIXED forms the FP32 node sums in units of the pair's distance (no power
+ * of a length above the square in FP32).  A field point lying on an element gets NaN in all six rows
  * (the normal field jumps there) and bemc_query_stats returns BEMC_W_ON_SURFACE.
  * Asynchronous like bemc_eval.  Errors: as bemc_eval. */
 int bemc_eval_gradient(bemc_handle h, const double* pts, int64_t n, int precision, int rhs,
@@ -265,7 +265,7 @@ int bemc_solve_densities(bemc_handle h, const double* potential, double* sigma, 
                          int restart, int precision, bemc_solve_info* info, void* stream);
 
 /* Size of the near-pair list (8 bytes per pair, plus 24 for its regrouping and 8 per
- * result row -- 4 for the field, 6 for the gradient -- allocated at the next evaluation;
+ * result row -- 4 for the field, 6 for the gradient, 1 otherwise -- allocated at the next evaluation;
  * 1 <= pairs <= 2^32 - 1).  grow != 0: the list starts at this size and grows to what an
  * evaluation needs (the default policy, starting at max(2^20, 8 n) pairs; the host reads
  * each evaluation's pair count before it enqueues the near field).  grow = 0: the size is
@@ -308,8 +308,8 @@ int bemc_query_stats(bemc_handle h, bemc_stats* out);
  * own, and one stream serves only that queue, so that short queries do not wait behind
  * long batches; the other streams take the long queue first and the short one when the
  * long one is empty.  A query's result depends on the other queries in its batch only
- * through the number of element chunks of the far-field launch (the summation grouping,
- * a rounding-level difference); with the rule choice by distance ratio also through the
+ * through the number of element chunks of the far-field launch and the lanes that add a point's
+ * sums (the summation grouping, a rounding-level difference); with the rule choice by distance ratio also through the
  * rule each wavefront of neighbouring points picks (an accuracy-level difference).
  * --------------------------------------------------------------------------------- */
 

@@ -1,13 +1,17 @@
 // HIP kernels for gfx950 (MI355X): Gaussian-cubature potential and field of charged
 // BEM triangles and rectangles (Glueck & Hilk, arXiv:1606.03743).
 //
+//  near_list_kernel    FP64 distance-ratio test (Sec. 2) behind boxes of points; near pairs
+//                      compacted per wavefront into a dense list.
 //  far_eval_kernel     PPT field points per lane; element tiles are staged in LDS with
 //                      their Gaussian points generated on the fly in each element's own
-//                      frame (Eq. 3.2 / 3.3); FP64 distance-ratio test per pair (Sec. 2), near
-//                      pairs compacted per wavefront into a dense list; far pairs summed as
-//                      point charges (Sec. 4, Eq. 4.1), potential and field from the same
-//                      nodes.  FP64 or mixed (FP32 node sums); one rule per element kind or
-//                      the rule chosen by distance ratio; field or field gradient.
+//                      frame (Eq. 3.2 / 3.3); the same test per pair leaves the near ones out;
+//                      far pairs summed as point charges (Sec. 4, Eq. 4.1), potential and field
+//                      from the same nodes.  FP64 or mixed (FP32 node sums); one rule per element
+//                      kind or the rule chosen by distance ratio; potential and field, potential
+//                      alone or field gradient.
+//  far_few_kernel      the same for at most 128 points: an element per lane, FP64 sums, the near
+//                      pairs listed in the same launch.
 //  far_colloc_kernel   the same sum, potential only, at element centroids, for up to eight
 //                      density vectors (matrix-free collocation product).
 //  near_kernel         FP64 near field over the dense list: each pair's recursive subdivision
@@ -275,8 +279,11 @@ constexpr int kListPoints = kBlock * kListPPT;
 constexpr int64_t kListFine = 1024;  // elements of a chunk from which the points' own boxes pay
 
 // FINE: with the points' own boxes, for long chunks (a short chunk's candidates are tested at once:
-// forming the boxes takes longer, 30 us).  Without them the kernel needs few enough registers and little
-// enough LDS to run beside another stream's far kernel, which a served batch of few points has to.
+// forming the boxes takes longer, 30 us).  87 registers and 56 bytes of scratch per lane, 62 and none
+// without the boxes, which is what fits beside four workgroups of another stream's mixed far kernel.
+// Served batches take either by the same rule (1,000,000 elements: FINE above 1,024 points); without
+// FINE there the latencies stay the same (40 queries/s by distance ratio: p50 36.6 and 35.7 ms, short queries
+// 25.3 and 24.3, p99 537 and 541).
 template <bool FINE>
 __global__ __launch_bounds__(kBlock) void near_list_kernel(const double* __restrict__ pts, int64_t n, Elements el,
                                                            NearPair* __restrict__ list, unsigned long long cap,
@@ -1958,9 +1965,12 @@ __device__ __forceinline__ void on_element_pairs(const NearArgs& a, unsigned lon
 }
 
 // A list of at most this many pairs is walked a wavefront per pair, breadth first, whatever the pairs'
-// depth: fewer than eight pairs per resident wavefront, the lanes' walks would leave most of the
-// chip idle (4,100 pairs: near stage 0.23 ms, 0.40 ms with the shallow pairs one per lane; 40,000:
-// 0.71 and 0.55 ms; 250,000: 2.5 and 0.7 ms).
+// depth: fewer than eleven pairs per resident wavefront, the lanes' walks would leave most of the
+// chip idle.  Near stage so, and with the pairs that are not deep one per lane (3,600 elements, field):
+// 16,500 pairs 0.41 and 0.63 ms, 34,600 pairs 0.28 and 0.50, 57,400 pairs 0.33 and 0.55, 107,000 pairs
+// 0.39 and 0.58, 174,000 pairs 0.52 and 0.68 (gradient 0.64 and 0.72).  The line lies where the two were
+// equal while a wavefront claimed its pairs one by one (40,000 pairs 0.71 and 0.55 ms); with several to a
+// claim it is on the safe side: the wavefronts stay the faster to past 174,000 pairs.
 constexpr unsigned long long kShortList = 32768;
 constexpr unsigned kNearWindow = 64;  // entries of the order a wavefront claims at a time
 constexpr unsigned long long kClaimMax = 8;  // deep pairs a wavefront claims at a time at most
@@ -2597,9 +2607,12 @@ template <bool DR, int NT, int NR, int T1, int T2, int T3, int R1, int R2, int R
 hipError_t far_eval_launch(const FarArgs& a, hipStream_t s)
 {
     // Batches of other streams run beside a served one: five workgroups of the mixed kernel with one point per
-    // lane (90 registers) would leave a CU 32 registers per lane, and the list pass (62) and the near
+    // lane (90 registers) would leave a CU 32 registers per lane, and the list pass (62 or 87) and the near
     // kernel (120) of a short batch would wait for its workgroups to end, each some milliseconds
     // long; four leave 128 (120 queries, 1,000,000 elements: p50 91 ms with five, 31 with four).
+    // The distance-ratio kernel with two points per lane (119 registers, four workgroups) gets no spare
+    // LDS: two workgroups a CU instead cost more than the short queries gain (40 queries/s, 1,000,000
+    // elements: short p50 25 -> 8 ms, but saturation 52 -> 37 queries/s and p99 0.54 -> 1.82 s).
     using Tile = TileLds<MIXED, 1, !MIXED && PPT == 1 && MODE != kFarGrad>;
     const size_t spare = a.beside && MIXED && PPT == 1 && sizeof(Tile) < kBesideLds ? kBesideLds - sizeof(Tile) : 0;
     const int64_t per = (int64_t)kBlock * PPT;
