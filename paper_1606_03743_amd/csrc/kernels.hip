@@ -2665,6 +2665,8 @@ hipError_t far_eval_dispatch(const FarArgs& a, hipStream_t s)
 // Potential alone: compiled for the default rules, the 7-point triangle rule and the levels.  FP64: 7
 // instead of 12 FP64 instructions per node beside the reciprocal square root, mixed 5 instead of 9, and
 // no rotation back (131,071 points x 150,000 elements by distance ratio, mixed: far kernel 85.0 -> 52.6 ms).
+// Other rules take the run-time kernel, which is still faster than the field's compiled ones (20,000 points x
+// 18,000 elements: 33-point / Table B5 4.7 and 6.4 ms, 12-point / 7 x 7 4.0 and 5.3; mixed 2.0 and 3.4, 1.8 and 2.5).
 template <bool MIXED>
 hipError_t far_phi_dispatch(const FarArgs& a, hipStream_t s)
 {
